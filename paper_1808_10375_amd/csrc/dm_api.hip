@@ -43,6 +43,9 @@ bool is_mixed(int F) { return F == 188 || F == 200; }
 // ---------------------------------------------------------------------------
 int n_pblk(int F) { return (F * F + 255) / 256; }
 
+// blocks of k_probe_final (one eps_P partial per mode each)
+int n_fblk(int F) { return (F * F + dmk::kFinalPix - 1) / dmk::kFinalPix; }
+
 // view chunks of the probe partial sums: about 1024 blocks of 256 pixels,
 // four per compute unit (dm_autotune chose half the earlier 2048 at 2500 x
 // 5 x 128^2, 10000 x 8 x 256^2 and 10000 x 4 x 188^2: 0.27 against 0.29 ms
@@ -196,7 +199,7 @@ ScanLayout scan_layout(const dm_desc& d) {
   L.err_psi = take((size_t)std::max({L.n_psi_parts_fused, L.n_psi_parts_multi, 2 * (int)N}) *
                    2 * 4);
   L.err_obj = take((size_t)L.ntiles16 * NL * 2 * 4);
-  L.err_probe = take((size_t)n_pblk((int)F) * d.n_modes * 2 * 4);
+  L.err_probe = take((size_t)n_fblk((int)F) * d.n_modes * 2 * 4);
   L.ring = take(sizeof(DevErrors) * dmk::kRing);
   L.counter = take(sizeof(int));
   L.mode_pow = take(DM_MAX_MODES * sizeof(double));
@@ -884,8 +887,8 @@ dm_status launch_iteration(dm_ctx* c, bool psi_err) {
     DM_LAUNCHED(c, "k_probe_partial");
     DM_TRY(phase_end(c, mk));
     DM_TRY(phase_begin(c, DM_PHASE_PROBE_FINAL, &mk));
-    hipLaunchKernelGGL(dmk::k_probe_final, dim3(nb, n), dim3(256), 0, c->stream, c->scan_dev(),
-                       M, FF);
+    hipLaunchKernelGGL(dmk::k_probe_final, dim3(n_fblk(F), n), dim3(64 * (dmk::kFinalModes + 1)), 0,
+                       c->stream, c->scan_dev(), M, FF);
     DM_LAUNCHED(c, "k_probe_final");
     return phase_end(c, mk);
   };
@@ -897,8 +900,8 @@ dm_status launch_iteration(dm_ctx* c, bool psi_err) {
     DM_TRY(probe());
   }
   DM_TRY(phase_begin(c, DM_PHASE_ERRORS, &mk));
-  hipLaunchKernelGGL(dmk::k_errors, dim3(n), dim3(256), 0, c->stream, c->scan_dev(), nb, M,
-                     c->flags_dev(), psi_valid ? 1 : 0);
+  hipLaunchKernelGGL(dmk::k_errors, dim3(n), dim3(dmk::kErrThreads), 0, c->stream, c->scan_dev(),
+                     n_fblk(F), M, c->flags_dev(), psi_valid ? 1 : 0);
   DM_LAUNCHED(c, "k_errors");
   DM_TRY(phase_end(c, mk));
   if (c->timing()) c->timed_iters++;

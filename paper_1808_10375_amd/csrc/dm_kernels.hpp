@@ -1444,59 +1444,81 @@ __global__ __launch_bounds__(256) void k_probe_partial(const ScanDev* __restrict
 // Probe update, stage 2: fixed-order sum over chunks, division (zero
 // denominators keep the old value), per-mode eps_P partials and the mode
 // power D = sum_k |P'_k|^2 used by the next object update.
-__global__ __launch_bounds__(256) void k_probe_final(const ScanDev* __restrict__ scans, int M,
-                                                     int FF) {
-  __shared__ float red[8];
+// A block owns kFinalPix pixels (one wave's lanes); one wave adds the chunks
+// of one mode (or of the denominator) in chunk order with 16 loads in flight.
+// With one thread adding all chunks of all modes of a pixel, eight loads at a
+// time, the kernel was a serial chain of loads on few compute units: 18.3 us
+// at 64 chunks x 3 modes x 64^2 and 8.4 us at 1 mode x 32^2, now 6.0 and 5.7
+// (launch included); the sums and their order are the same.
+constexpr int kFinalPix = 64;
+constexpr int kFinalModes = 8;  // waves for modes, and one for the denominator
+__global__ __launch_bounds__(64 * (kFinalModes + 1)) void k_probe_final(
+    const ScanDev* __restrict__ scans, int M, int FF) {
+  constexpr int NM = kFinalModes;
+  __shared__ float pden[64];
+  __shared__ float p2[16][64];  // |P'_m|^2
   const ScanDev& sc = scans[blockIdx.y];
-  const float2* __restrict__ num_part = sc.num_part;
-  const float* __restrict__ den_part = sc.den_part;
   float2* __restrict__ P = sc.P;
-  float* __restrict__ D = sc.D;
   float* __restrict__ err_probe = sc.err_probe;
-  const int C = sc.C;
-  // pixels past F * F (frames whose F * F is not a multiple of 256) read
-  // pixel 0 and store nothing; they stay for the block sums' barriers
-  const bool in = blockIdx.x * 256 + threadIdx.x < FF;
-  const int pix = in ? blockIdx.x * 256 + threadIdx.x : 0;
-  // chunk partials are added in chunk order; loads go out in batches of 8
-  float den = 0.f;
-  int cc = 0;
-  for (; cc + 8 <= C; cc += 8) {
-    float v[8];
+  const int C = uni(sc.C);
+  const int lane = threadIdx.x & 63, w = uni(threadIdx.x >> 6);
+  // pixels past F * F (frames whose F * F is not a multiple of 64) read
+  // pixel 0 and store nothing; they stay for the barriers
+  const bool in = blockIdx.x * 64 + lane < FF;
+  const int pix = in ? blockIdx.x * 64 + lane : 0;
+  constexpr int U = 16;  // loads in flight
+  if (w == NM) {
+    const float* __restrict__ dp = sc.den_part + pix;
+    float den = 0.f;
+    for (int cc = 0; cc < C; cc += U) {
+      float v[U];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = den_part[(size_t)(cc + k) * FF + pix];
+      for (int k = 0; k < U; ++k) v[k] = cc + k < C ? dp[(size_t)(cc + k) * FF] : 0.f;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) den += v[k];
+      for (int k = 0; k < U; ++k) den += v[k];
+    }
+    pden[lane] = den;
   }
-  for (; cc < C; ++cc) den += den_part[(size_t)cc * FF + pix];
-  float dsum = 0.f;
-  for (int m = 0; m < M; ++m) {
-    float2 num = make_float2(0.f, 0.f);
-    int c2 = 0;
-    for (; c2 + 8 <= C; c2 += 8) {
-      float2 v[8];
+  for (int mg = 0; mg < M; mg += NM) {
+    const int m = mg + w;
+    const bool mine = w < NM && m < M;
+    float2 num = make_float2(0.f, 0.f), po = num;
+    if (mine) {
+      const float2* __restrict__ np = sc.num_part + (size_t)m * FF + pix;
+      po = P[(size_t)m * FF + pix];
+      for (int cc = 0; cc < C; cc += U) {
+        float2 v[U];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = num_part[((size_t)(c2 + k) * M + m) * FF + pix];
+        for (int k = 0; k < U; ++k)
+          v[k] = cc + k < C ? np[(size_t)(cc + k) * M * FF] : make_float2(0.f, 0.f);
 #pragma unroll
-      for (int k = 0; k < 8; ++k) num = cadd(num, v[k]);
+        for (int k = 0; k < U; ++k) num = cadd(num, v[k]);
+      }
     }
-    for (; c2 < C; ++c2) num = cadd(num, num_part[((size_t)c2 * M + m) * FF + pix]);
-    const float2 po = P[(size_t)m * FF + pix];
-    float2 pn = po;
-    if (den > 0.f) {
-      const float inv = 1.0f / den;
-      pn = make_float2(num.x * inv, num.y * inv);
-    }
-    if (in) P[(size_t)m * FF + pix] = pn;
-    float e_d = in ? cabs2(csub(pn, po)) : 0.f, e_n = in ? cabs2(pn) : 0.f;
-    dsum += e_n;
-    block_sum2<256>(e_d, e_n, red);
-    if (threadIdx.x == 0) {
-      err_probe[((size_t)blockIdx.x * M + m) * 2] = e_d;
-      err_probe[((size_t)blockIdx.x * M + m) * 2 + 1] = e_n;
+    if (mg == 0) __syncthreads();  // the denominator
+    if (mine) {
+      const float den = pden[lane];
+      float2 pn = po;
+      if (den > 0.f) {
+        const float inv = 1.0f / den;
+        pn = make_float2(num.x * inv, num.y * inv);
+      }
+      if (in) P[(size_t)m * FF + pix] = pn;
+      const float q = in ? cabs2(pn) : 0.f;
+      p2[m][lane] = q;
+      const float e_d = wave_sum(in ? cabs2(csub(pn, po)) : 0.f), e_n = wave_sum(q);
+      if (lane == 0) {
+        err_probe[((size_t)blockIdx.x * M + m) * 2] = e_d;
+        err_probe[((size_t)blockIdx.x * M + m) * 2 + 1] = e_n;
+      }
     }
   }
-  if (in) D[pix] = dsum;
+  __syncthreads();
+  if (w == 0 && in) {
+    float d = 0.f;
+    for (int m = 0; m < M; ++m) d += p2[m][lane];
+    sc.D[pix] = d;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1516,6 +1538,13 @@ __device__ double block_sum_d(double x, double* red) {
   return r;
 }
 
+// Sum over the wave's lanes (every lane gets it; fixed order)
+__device__ __forceinline__ double wave_sum_d(double x) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+  return x;
+}
+
 // sqrt(d / n) of two sums of squares; 0/0 is 0, d/0 infinite, and a NaN in
 // either sum stays NaN (so a diverged iteration is never reported as 0)
 __device__ __forceinline__ float rel_norm(double d, double n) {
@@ -1525,54 +1554,82 @@ __device__ __forceinline__ float rel_norm(double d, double n) {
 
 // psi_valid = 0: this iteration's view kernel formed no eps_psi partials;
 // eps_psi is then reported as NaN and not taken for divergence.
-__global__ __launch_bounds__(256) void k_errors(const ScanDev* __restrict__ scans, int n_pblk,
-                                                int M, int* __restrict__ flags, int psi_valid) {
-  __shared__ double red[256];
+// One block of 16 waves per scan.  All threads stride over the views' and the
+// object's partials with four loads in flight; wave m alone adds the probe
+// partials of mode m.  Bound by the latency of those loads: with 256 threads,
+// one load in flight and a barrier tree per sum it took 103 us at 58 k view
+// partials (2521 views of 200^2) and 11.5 us at 407 views x 3 modes of 64^2,
+// now 17.0 and 6.1 us.
+constexpr int kErrThreads = 1024;
+__global__ __launch_bounds__(kErrThreads) void k_errors(const ScanDev* __restrict__ scans,
+                                                        int n_pblk, int M,
+                                                        int* __restrict__ flags,
+                                                        int psi_valid) {
+  constexpr int NT = kErrThreads, NW = NT / 64;
+  __shared__ double red[NW][4];
+  __shared__ double pm[16][2];
   const ScanDev& sc = scans[blockIdx.x];
-  const float* __restrict__ err_psi = sc.err_psi;
-  const float* __restrict__ err_obj = sc.err_obj;
-  const float* __restrict__ err_probe = sc.err_probe;
-  int* __restrict__ counter = sc.counter;
-  DevErrors* __restrict__ ring = sc.ring;
-  const int n_psi = sc.n_psi_parts, n_obj = sc.ntiles * sc.L;
-  const int t = threadIdx.x;
-  double v[4];
-  double s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-  for (int i = t; i < n_psi; i += 256) { s0 += err_psi[2 * i]; s1 += err_psi[2 * i + 1]; }
-  for (int i = t; i < n_obj; i += 256) { s2 += err_obj[2 * i]; s3 += err_obj[2 * i + 1]; }
-  v[0] = block_sum_d(s0, red);
-  v[1] = block_sum_d(s1, red);
-  v[2] = block_sum_d(s2, red);
-  v[3] = block_sum_d(s3, red);
-  double pd_tot = 0, pn_tot = 0;
-  float modes[16];
-  for (int m = 0; m < M; ++m) {
-    double a = 0, b = 0;
-    for (int i = t; i < n_pblk; i += 256) {
-      a += err_probe[((size_t)i * M + m) * 2];
-      b += err_probe[((size_t)i * M + m) * 2 + 1];
+  const float2* __restrict__ err_psi = reinterpret_cast<const float2*>(sc.err_psi);
+  const float2* __restrict__ err_obj = reinterpret_cast<const float2*>(sc.err_obj);
+  const float2* __restrict__ err_probe = reinterpret_cast<const float2*>(sc.err_probe);
+  const int n_psi = psi_valid ? sc.n_psi_parts : 0, n_obj = sc.ntiles * sc.L;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  // sums over i = first, first + step, ... < n of both components, four
+  // loads at a time
+  auto sum2 = [](const float2* __restrict__ p, int first, int step, int n, double& a, double& b) {
+    constexpr int U = 4;
+    int i = first;
+#pragma unroll 1
+    for (; i + (U - 1) * step < n; i += U * step) {
+      float2 v[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) v[k] = p[i + k * step];
+#pragma unroll
+      for (int k = 0; k < U; ++k) { a += v[k].x; b += v[k].y; }
     }
-    a = block_sum_d(a, red);
-    b = block_sum_d(b, red);
-    pd_tot += a;
-    pn_tot += b;
-    modes[m] = rel_norm(a, b);
+#pragma unroll 1
+    for (; i < n; i += step) { a += p[i].x; b += p[i].y; }
+  };
+  double s[4] = {0, 0, 0, 0};
+  sum2(err_psi, t, NT, n_psi, s[0], s[1]);
+  sum2(err_obj, t, NT, n_obj, s[2], s[3]);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) s[k] = wave_sum_d(s[k]);
+  if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) red[w][k] = s[k];
   }
+  for (int m = w; m < M; m += NW) {
+    double a = 0, b = 0;
+    sum2(err_probe + m, lane * M, 64 * M, (n_pblk - 1) * M + 1, a, b);
+    a = wave_sum_d(a);
+    b = wave_sum_d(b);
+    if (lane == 0) { pm[m][0] = a; pm[m][1] = b; }
+  }
+  __syncthreads();
   if (t == 0) {
-    const int it = *counter;
-    DevErrors e;
+    double v[4] = {0, 0, 0, 0};
+    for (int i = 0; i < NW; ++i)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] += red[i][k];
+    double pd_tot = 0, pn_tot = 0;
+    for (int m = 0; m < M; ++m) { pd_tot += pm[m][0]; pn_tot += pm[m][1]; }
+    const int it = *sc.counter;
+    DevErrors& e = sc.ring[it % kRing];
+    const float e_psi = !psi_valid ? NAN : rel_norm(v[0], v[1]);
+    const float e_obj = rel_norm(v[2], v[3]), e_probe = rel_norm(pd_tot, pn_tot);
+    bool bad = (psi_valid && !isfinite(e_psi)) || !isfinite(e_obj) || !isfinite(e_probe);
     e.iter = it + 1;
-    e.eps_psi = !psi_valid ? NAN : rel_norm(v[0], v[1]);
-    e.eps_obj = rel_norm(v[2], v[3]);
-    e.eps_probe = rel_norm(pd_tot, pn_tot);
-    bool bad = (psi_valid && !isfinite(e.eps_psi)) || !isfinite(e.eps_obj) ||
-               !isfinite(e.eps_probe);
+    e.eps_psi = e_psi;
+    e.eps_obj = e_obj;
+    e.eps_probe = e_probe;
+#pragma unroll 1
     for (int m = 0; m < 16; ++m) {
-      e.eps_mode[m] = (m < M) ? modes[m] : 0.f;
-      if (m < M && !isfinite(modes[m])) bad = true;
+      const float em = (m < M) ? rel_norm(pm[m][0], pm[m][1]) : 0.f;
+      e.eps_mode[m] = em;
+      if (!isfinite(em)) bad = true;
     }
-    ring[it % kRing] = e;
-    *counter = it + 1;
+    *sc.counter = it + 1;
     if (bad) atomicOr(flags + 1 + blockIdx.x, 1);
   }
 }
