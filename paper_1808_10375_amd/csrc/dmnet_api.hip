@@ -10,7 +10,7 @@
 #include <vector>
 
 #include "../../include/dmnet.h"
-#include "dmnet_kernels.hpp"
+#include "dmnet_conv.hpp"
 
 namespace {
 
@@ -21,6 +21,15 @@ struct Conv {
   int cin, cout, k, level;
   size_t w_off, b_off;  // offsets (in floats) into the parameter vector
 };
+
+// Whether the 3x3 convolutions run on activations kept in chunk layout
+// (dmnet_conv.hpp): every channel count but the input's is then a multiple of
+// 32.  Other widths keep the kernels that gather their operands: their sums
+// run channel by channel over the taps, an order that chunks cannot follow,
+// and another order flips bfloat16 roundings of later layers.
+bool chunked(const dmnet_desc& d) {
+  return !(d.flags & DMNET_FLAG_FP32_WEIGHTS) && d.base_ch % 32 == 0;
+}
 
 // pixels per block of the matrix-core weight gradient (a multiple of 32)
 constexpr int kWgradChunk = 1024;
@@ -101,8 +110,38 @@ ActLayout act_layout(const dmnet_desc& d, const Shape& s) {
   return a;
 }
 
+// The same activations as bfloat16 in chunk layout, as the 3x3 convolutions
+// read them (offsets in values; each buffer holds `batch` samples)
+struct Act16Layout {
+  std::vector<size_t> enc_mid, enc_out, pool, dec_mid, dec_out;
+  size_t total;
+};
+
+Act16Layout act16_layout(const dmnet_desc& d, const Shape& s) {
+  Act16Layout a;
+  size_t off = 0;
+  auto take = [&](size_t c, size_t hw) {
+    size_t o = off;
+    off += c * hw * d.batch;
+    off = (off + 127) / 128 * 128;
+    return o;
+  };
+  for (int l = 0; l < d.levels; ++l) {
+    const size_t S = (size_t)(d.size >> l), HW = S * S;
+    a.enc_mid.push_back(take(s.ch[l], HW));
+    a.enc_out.push_back(take(s.ch[l], HW));
+    if (l < d.levels - 1) {
+      a.pool.push_back(take(s.ch[l], HW / 4));
+      a.dec_mid.push_back(take(s.ch[l], HW));
+      a.dec_out.push_back(take(s.ch[l], HW));
+    }
+  }
+  a.total = off;
+  return a;
+}
+
 struct NetLayout {
-  size_t params, wb, wbT, wbK, wTK, grads, m, v, acts, grad_acts, xcl, wgb, wpart, partial,
+  size_t params, wb, wbT, wbK, wTK, wpf, wpt, grads, m, v, acts, grad_acts, acts16, xcl, wgb, wpart, partial,
       loss, total;
 };
 
@@ -130,16 +169,23 @@ NetLayout net_layout(const dmnet_desc& d, const Shape& s, const ActLayout& a) {
   };
   L.params = take(s.n_params * 4);
   L.wb = take(s.n_params * 2);
-  L.wbT = take(s.n_params * 2);  // flipped, transposed 3x3 weights (data gradient)
-  L.wbK = take(s.n_params * 2);  // tap-major 3x3 weights [o][t][c]
-  L.wTK = take(s.n_params * 2);  // tap-major flipped, transposed [c][t][o]
+  if (chunked(d)) {
+    // 3x3 weights in fragment order, at their offsets in the parameters
+    L.wpf = take(s.n_params * 2);
+    L.wpt = take(s.n_params * 2);
+    L.acts16 = take(act16_layout(d, s).total * 2);
+  } else {
+    L.wbT = take(s.n_params * 2);  // flipped, transposed 3x3 weights (data gradient)
+    L.wbK = take(s.n_params * 2);  // tap-major 3x3 weights [o][t][c]
+    L.wTK = take(s.n_params * 2);  // tap-major flipped, transposed [c][t][o]
+  }
   L.grads = take(s.n_params * 4);
   L.m = take(s.n_params * 4);
   L.v = take(s.n_params * 4);
   L.acts = take(a.total * 4 * d.batch);
   L.grad_acts = take(a.total * 4 * d.batch);
-  // channel-last bfloat16 copy of a 3x3 convolution's input (or output
-  // gradient), one convolution at a time
+  // bfloat16 copy of a 3x3 convolution's input or output gradient (channel
+  // last or chunk layout), one convolution at a time
   size_t xcl = 8;
   for (const Conv& c : s.convs)
     if (c.k == 3) {
@@ -177,6 +223,7 @@ struct dmnet {
   dmnet_desc d;
   Shape s;
   ActLayout a;
+  Act16Layout a16;
   NetLayout L;
   char* ws = nullptr;
   hipStream_t stream = nullptr;
@@ -189,8 +236,12 @@ struct dmnet {
   uint16_t* wbT() { return reinterpret_cast<uint16_t*>(ws + L.wbT); }
   uint16_t* wbK() { return reinterpret_cast<uint16_t*>(ws + L.wbK); }
   uint16_t* wTK() { return reinterpret_cast<uint16_t*>(ws + L.wTK); }
+  uint16_t* wpf() { return reinterpret_cast<uint16_t*>(ws + L.wpf); }
+  uint16_t* wpt() { return reinterpret_cast<uint16_t*>(ws + L.wpt); }
+  uint16_t* act16(size_t o) { return reinterpret_cast<uint16_t*>(ws + L.acts16) + o; }
   uint16_t* xcl() { return reinterpret_cast<uint16_t*>(ws + L.xcl); }
   uint16_t* wgb() { return reinterpret_cast<uint16_t*>(ws + L.wgb); }
+  bool chunked() const { return ::chunked(d); }
   bool mfma() const { return !(d.flags & DMNET_FLAG_FP32_WEIGHTS); }
   float* grads() { return f(L.grads); }
   float* act(size_t o) { return f(L.acts) + o; }     // per-sample stride a.total
@@ -235,26 +286,102 @@ dm_status check(dmnet* n, int count) {
 
 unsigned grid_for(long n) { return (unsigned)std::min<long>((n + 255) / 256, 8192); }
 
-// the flipped, transposed bfloat16 weights of every 3x3 convolution, the A
-// operand of the matrix-core data gradient; redone whenever the weights change
-dm_status refresh_transposed(dmnet* net) {
+// the copies of every 3x3 convolution's weights that the matrix-core kernels
+// read; redone whenever the weights change
+dm_status refresh_packed(dmnet* net) {
   if (!net->mfma()) return DM_OK;
   for (const Conv& c : net->s.convs) {
     if (c.k != 3) continue;
-    const long cnt = (long)c.cout * c.cin * 9;
-    hipLaunchKernelGGL(dmn::k_flip_transpose3, dim3(grid_for(cnt)), dim3(256), 0, net->stream,
-                       net->wb() + c.w_off, c.cout, c.cin, net->wbT() + c.w_off);
-    hipLaunchKernelGGL(dmn::k_tapmajor3, dim3(grid_for(cnt)), dim3(256), 0, net->stream,
-                       net->wb() + c.w_off, c.cout, c.cin, net->wbK() + c.w_off,
-                       net->wTK() + c.w_off);
+    if (!net->chunked()) {
+      const long cnt = (long)c.cout * c.cin * 9;
+      hipLaunchKernelGGL(dmn::k_flip_transpose3, dim3(grid_for(cnt)), dim3(256), 0, net->stream,
+                         net->wb() + c.w_off, c.cout, c.cin, net->wbT() + c.w_off);
+      hipLaunchKernelGGL(dmn::k_tapmajor3, dim3(grid_for(cnt)), dim3(256), 0, net->stream,
+                         net->wb() + c.w_off, c.cout, c.cin, net->wbK() + c.w_off,
+                         net->wTK() + c.w_off);
+      continue;
+    }
+    if (c.cin % 32) continue;  // the first convolution reads wb
+    hipLaunchKernelGGL(dmn::k_pack3, dim3(grid_for(2L * c.cout * c.cin * 9)), dim3(256), 0,
+                       net->stream, net->wb() + c.w_off, c.cout, c.cin, net->wpf() + c.w_off,
+                       net->wpt() + c.w_off);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     net->failed = true;
-    net->err = std::string("k_flip_transpose3: ") + hipGetErrorString(e);
+    net->err = std::string("weight copies: ") + hipGetErrorString(e);
     return DM_E_HIP;
   }
   return DM_OK;
+}
+
+// LDS of a block: two weight groups and the staged run of as many chunks as
+// fit beside them, all of them where they do; half of a compute unit's for
+// blocks of 4 waves, all of it for 8
+constexpr size_t conv3_lds(int nw) { return (size_t)nw * 20 * 1024; }
+
+template <class C>
+size_t conv3_chunk_bytes(int W) {
+  return (size_t)(C::TP + 2 + 2 * dmn::conv_row_step(C::TP, W)) * 64;
+}
+
+struct ConvCall {
+  dmn::ConvSrc s0, s1;
+  int H, W, n;
+  const uint16_t* A;
+  const float* bias;
+  uint16_t* y16;
+  float* y32;
+  int yc;
+  long y_ns;
+  bool relu;
+  long positions() const { return (long)n * (H + 1) * (W + 1); }
+  int chunks() const { return s0.nch + s1.nch; }
+};
+
+template <int OT, int PT, int WO, int NW>
+struct ConvTile {
+  using C = dmn::ConvCfg<OT, PT, WO, NW>;
+  static constexpr size_t kWeights = (size_t)2 * 16 * C::WG;
+  // all input channels in LDS and at least `blocks` blocks
+  static bool fits(const ConvCall& c, long blocks) {
+    return (c.positions() + C::TP - 1) / C::TP * (c.yc / C::TO) >= blocks &&
+           c.chunks() * conv3_chunk_bytes<C>(c.W) + kWeights <= conv3_lds(NW);
+  }
+  static dm_status launch(dmnet* net, const ConvCall& c) {
+    const size_t per = conv3_chunk_bytes<C>(c.W);
+    const int grp = std::min(c.chunks(), (int)((conv3_lds(NW) - kWeights) / per));
+    const dmn::FastDiv dps((uint32_t)((c.H + 1) * (c.W + 1))), dpw((uint32_t)(c.W + 1));
+    const dim3 g((unsigned)((c.positions() + C::TP - 1) / C::TP), (unsigned)(c.yc / C::TO));
+    NET_HIP(net, hipFuncSetAttribute(reinterpret_cast<const void*>(dmn::k_conv3<OT, PT, WO, NW>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)conv3_lds(NW)));
+    hipLaunchKernelGGL((dmn::k_conv3<OT, PT, WO, NW>), g, dim3(64 * NW), kWeights + grp * per,
+                       net->stream, c.s0, c.s1, c.H, c.W, c.n, dps, dpw, grp, c.A, c.bias, c.y16,
+                       c.y32, c.yc, c.y_ns, c.relu ? 1 : 0);
+    NET_LAUNCHED(net, "k_conv3");
+    return DM_OK;
+  }
+};
+
+// The block tile of a 3x3 matrix-core convolution (output channels x
+// positions): the largest that holds all input channels in LDS and still
+// gives the 256 compute units two blocks of 4 waves or one of 8; else the
+// smallest, whose blocks stage the channels in groups for every tap.
+dm_status conv3(dmnet* net, const ConvCall& c) {
+  if (c.yc % 64 == 0) {
+    if (ConvTile<4, 4, 1, 4>::fits(c, 512)) return ConvTile<4, 4, 1, 4>::launch(net, c);
+    if (ConvTile<2, 4, 2, 4>::fits(c, 512)) return ConvTile<2, 4, 2, 4>::launch(net, c);
+    if (ConvTile<2, 4, 2, 8>::fits(c, 256)) return ConvTile<2, 4, 2, 8>::launch(net, c);
+    if (ConvTile<2, 2, 2, 4>::fits(c, 512)) return ConvTile<2, 2, 2, 4>::launch(net, c);
+    if (ConvTile<2, 2, 2, 8>::fits(c, 256)) return ConvTile<2, 2, 2, 8>::launch(net, c);
+    if (ConvTile<2, 2, 2, 4>::fits(c, 1)) return ConvTile<2, 2, 2, 4>::launch(net, c);
+    return ConvTile<2, 2, 2, 8>::launch(net, c);
+  }
+  if (ConvTile<2, 4, 1, 4>::fits(c, 512)) return ConvTile<2, 4, 1, 4>::launch(net, c);
+  if (ConvTile<2, 4, 1, 8>::fits(c, 256)) return ConvTile<2, 4, 1, 8>::launch(net, c);
+  if (ConvTile<1, 4, 2, 4>::fits(c, 1)) return ConvTile<1, 4, 2, 4>::launch(net, c);
+  return ConvTile<1, 4, 2, 8>::launch(net, c);
 }
 
 // y = conv(x) (+ ReLU); x, y are per-sample-strided tensors
@@ -349,7 +476,7 @@ dm_status conv_bwd(dmnet* net, const Conv& c, const float* x, long x_ns, const f
     hipLaunchKernelGGL(dmn::k_sum_chunks, dim3(grid_for(c.cout)), dim3(256), 0, net->stream,
                        part, bch, (long)c.cout, db);
     NET_LAUNCHED(net, "k_sum_chunks (bias)");
-    if (dx) {
+    if (dx && !net->chunked()) {
       dim3 g((unsigned)(((long)n * H * W + 255) / 256), (c.cin + 31) / 32);
       if (c.cout % 32 == 0 && c.w_off % 8 == 0) {
         const long cnt = (long)n * H * W * (c.cout / 8);
@@ -364,6 +491,14 @@ dm_status conv_bwd(dmnet* net, const Conv& c, const float* x, long x_ns, const f
                            z_ns, n, net->wbT() + c.w_off, nullptr, dx, c.cin, dx_ns, 0);
         NET_LAUNCHED(net, "k_conv3_mfma (data gradient)");
       }
+    }
+    if (dx && net->chunked()) {
+      const long cnt = (long)n * H * W * (c.cout / 8);
+      hipLaunchKernelGGL(dmn::k_to_chunk16, dim3(grid_for(cnt)), dim3(256), 0, net->stream, dz,
+                         c.cout, H * W, z_ns, n, net->xcl());
+      NET_LAUNCHED(net, "k_to_chunk16 (output gradient)");
+      NET_TRY(conv3(net, {{net->xcl(), c.cout / 32, 0}, {nullptr, 0, 0}, H, W, n,
+                          net->wpt() + c.w_off, nullptr, nullptr, dx, c.cin, dx_ns, false}));
     }
     return DM_OK;
   }
@@ -423,8 +558,78 @@ dm_status relu_mask(dmnet* net, float* g, const float* act, long ns, long per, i
   return DM_OK;
 }
 
-// forward pass; output into y (per-sample stride y_ns)
-dm_status forward(dmnet* net, const float* x, int n, float* y, long y_ns) {
+// Forward pass with the 3x3 convolutions on the matrix cores: every
+// activation is written in chunk layout; in float32 too where something
+// reads it so (the pooling and the head), and all of them for the backward
+// pass if keep32.
+dm_status forward_chunked(dmnet* net, const float* x, int n, float* y, long y_ns, bool keep32) {
+  const dmnet_desc& d = net->d;
+  const Shape& s = net->s;
+  const ActLayout& a = net->a;
+  const Act16Layout& h16 = net->a16;
+  const long T = (long)a.total;
+  const int L = d.levels;
+  int ci = 0;
+  auto run = [&](const Conv& c, dmn::ConvSrc s0, dmn::ConvSrc s1, uint16_t* y16, float* y32,
+                 int S) {
+    return conv3(net, {s0, s1, S, S, n, net->wpf() + c.w_off, net->params() + c.b_off, y16, y32,
+                       c.cout, T, true});
+  };
+  auto chunks = [&](int l) { return s.ch[l] / 32; };
+  const dmn::ConvSrc none{nullptr, 0, 0};
+  for (int l = 0; l < L; ++l) {
+    const int S = d.size >> l;
+    float* mid32 = keep32 ? net->act(a.enc_mid[l]) : nullptr;
+    if (l == 0) {
+      const Conv& c = s.convs[ci++];
+      hipLaunchKernelGGL(dmn::k_conv3_first, dim3((unsigned)(((long)n * S * S + 255) / 256),
+                                                  (unsigned)chunks(0)),
+                         dim3(256), 0, net->stream, x, S, S, (long)S * S, n, net->wb() + c.w_off,
+                         net->params() + c.b_off, net->act16(h16.enc_mid[0]), mid32, T);
+      NET_LAUNCHED(net, "k_conv3_first");
+    } else {
+      NET_TRY(run(s.convs[ci++], {net->act16(h16.pool[l - 1]), chunks(l - 1), 0}, none,
+                  net->act16(h16.enc_mid[l]), mid32, S));
+    }
+    const bool out32 = keep32 || l < L - 1;
+    NET_TRY(run(s.convs[ci++], {net->act16(h16.enc_mid[l]), chunks(l), 0}, none,
+                net->act16(h16.enc_out[l]), out32 ? net->act(a.enc_out[l]) : nullptr, S));
+    if (l < L - 1) {
+      const long tot = (long)n * (S / 2) * (S / 2) * (s.ch[l] / 8);
+      hipLaunchKernelGGL(dmn::k_avgpool2_chunk, dim3(grid_for(tot)), dim3(256), 0, net->stream,
+                         net->act(a.enc_out[l]), T, net->act16(h16.pool[l]),
+                         keep32 ? net->act(a.pool[l]) : nullptr, T, s.ch[l], S, S, n);
+      NET_LAUNCHED(net, "k_avgpool2_chunk");
+    }
+  }
+  const uint16_t* h = net->act16(h16.enc_out[L - 1]);
+  for (int l = L - 2; l >= 0; --l) {
+    const int S = d.size >> l;
+    if (keep32) {
+      const float* h32 = net->act(l == L - 2 ? a.bott : a.dec_out[l + 1]);
+      const long tot = (long)s.ch[l + 1] * S * S * n;
+      hipLaunchKernelGGL(dmn::k_upsample2, dim3(grid_for(tot)), dim3(256), 0, net->stream, h32, T,
+                         net->act(a.cat[l]), T, s.ch[l + 1], S / 2, S / 2, n);
+      NET_LAUNCHED(net, "k_upsample2");
+    }
+    NET_TRY(run(s.convs[ci++], {h, chunks(l + 1), 1},
+                {net->act16(h16.enc_out[l]), chunks(l), 0}, net->act16(h16.dec_mid[l]),
+                keep32 ? net->act(a.dec_mid[l]) : nullptr, S));
+    const bool out32 = keep32 || l == 0;
+    NET_TRY(run(s.convs[ci++], {net->act16(h16.dec_mid[l]), chunks(l), 0}, none,
+                l > 0 ? net->act16(h16.dec_out[l]) : nullptr,
+                out32 ? net->act(a.dec_out[l]) : nullptr, S));
+    h = net->act16(h16.dec_out[l]);
+  }
+  NET_TRY(conv_fwd(net, s.convs[ci++], net->act(a.dec_out[0]), T, y, y_ns, d.size, d.size, n,
+                   false));
+  return DM_OK;
+}
+
+// forward pass; output into y (per-sample stride y_ns); keep32: leave every
+// activation for the backward pass
+dm_status forward(dmnet* net, const float* x, int n, float* y, long y_ns, bool keep32) {
+  if (net->chunked()) return forward_chunked(net, x, n, y, y_ns, keep32);
   const dmnet_desc& d = net->d;
   const Shape& s = net->s;
   const ActLayout& a = net->a;
@@ -520,7 +725,7 @@ dm_status loss_and_grad(dmnet* net, const float* x, const float* target, int n) 
   const ActLayout& a = net->a;
   const long T = (long)a.total;
   const long per = 2L * net->d.size * net->d.size;
-  NET_TRY(forward(net, x, n, net->act(a.y), T));
+  NET_TRY(forward(net, x, n, net->act(a.y), T, true));
   // the outputs of the n samples sit T floats apart: one block per sample,
   // each leaving its sum of squares in partial[k]; the loss averages over
   // all n * per outputs
@@ -558,6 +763,7 @@ dm_status dmnet_create(dmnet** out, const dmnet_desc* d, void* ws, size_t ws_byt
   n->d = *d;
   n->s = make_shape(*d);
   n->a = act_layout(*d, n->s);
+  n->a16 = act16_layout(*d, n->s);
   n->L = net_layout(*d, n->s, n->a);
   if (ws_bytes < n->L.total) {
     delete n;
@@ -574,7 +780,7 @@ dm_status dmnet_create(dmnet** out, const dmnet_desc* d, void* ws, size_t ws_byt
                      0.f);
   hipLaunchKernelGGL(dmn::k_to_bf16, dim3(grid_for(P)), dim3(256), 0, n->stream, n->params(),
                      n->wb(), P);
-  if (hipGetLastError() != hipSuccess || refresh_transposed(n) != DM_OK) {
+  if (hipGetLastError() != hipSuccess || refresh_packed(n) != DM_OK) {
     delete n;
     return DM_E_HIP;
   }
@@ -590,7 +796,7 @@ dm_status dmnet_set_params(dmnet* n, const float* p) {
   hipLaunchKernelGGL(dmn::k_to_bf16, dim3(grid_for(P)), dim3(256), 0, n->stream, n->params(),
                      n->wb(), P);
   NET_LAUNCHED(n, "k_to_bf16");
-  NET_TRY(refresh_transposed(n));
+  NET_TRY(refresh_packed(n));
   hipLaunchKernelGGL(dmn::k_fill, dim3(grid_for(P)), dim3(256), 0, n->stream, n->f(n->L.m), P,
                      0.f);
   hipLaunchKernelGGL(dmn::k_fill, dim3(grid_for(P)), dim3(256), 0, n->stream, n->f(n->L.v), P,
@@ -611,7 +817,7 @@ dm_status dmnet_get_params(dmnet* n, float* p) {
 dm_status dmnet_forward(dmnet* n, const float* x, float* y, int32_t count) {
   NET_TRY(check(n, count));
   if (!x || !y) return DM_E_ARG;
-  return forward(n, x, count, y, 2L * n->d.size * n->d.size);
+  return forward(n, x, count, y, 2L * n->d.size * n->d.size, false);
 }
 
 dm_status dmnet_loss_grad(dmnet* n, const float* x, const float* target, int32_t count,
@@ -647,7 +853,7 @@ dm_status dmnet_train_step(dmnet* n, const float* x, const float* target, int32_
                      n->f(n->L.m), n->f(n->L.v), n->grads(), n->wb(), P, n->d.lr, n->d.beta1,
                      n->d.beta2, n->d.eps, c1, c2);
   NET_LAUNCHED(n, "k_adam");
-  return refresh_transposed(n);
+  return refresh_packed(n);
 }
 
 dm_status dmnet_preprocess(dmnet* n, const float* I, int32_t count, int32_t frame, float* x) {

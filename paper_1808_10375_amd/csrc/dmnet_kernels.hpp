@@ -48,6 +48,7 @@ __global__ __launch_bounds__(256) void k_conv(const float* __restrict__ x, int x
   float acc[COB];
 #pragma unroll
   for (int o = 0; o < COB; ++o) acc[o] = (!TRANS && bias && o0 + o < yc) ? bias[o0 + o] : 0.f;
+#pragma unroll(K == 1 ? 8 : 1)
   for (int c = 0; c < xc; ++c) {
     float xv[KK];
 #pragma unroll
