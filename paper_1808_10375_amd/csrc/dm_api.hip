@@ -695,23 +695,6 @@ dm_status launch_views_mixed(dm_ctx* c, bool direct) {
   return DM_OK;
 }
 
-// BF16x3 form: three persistent kernels, one block per CU, each holding the
-// split DFT matrix in LDS
-constexpr size_t kMfLdsW = sizeof(uint4) * dmk::kMfWords;
-constexpr size_t kMfLdsCols = kMfLdsW + 2 * 4 * dmk::kMfKs * 64 * 16;  // 160 KB
-
-hipError_t set_mfma_lds() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(dmk::k_mf_rows_fwd),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMfLdsW);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(dmk::k_mf_cols),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMfLdsCols);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(dmk::k_mf_rows_inv),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMfLdsW);
-  return e;
-}
-
 // The split DFT matrix in B-fragment order (see dm_mfma.hpp): W[a][b] =
 // exp(-2 pi i ab / F) in double, rounded to float, split into bfloat16 hi
 // and lo = bf16(x - hi), both rounded to nearest even.
@@ -750,7 +733,8 @@ std::vector<uint4> mfma_dft_table() {
   return out;
 }
 
-int mfma_grid(dm_ctx* c, int items) {
+// BF16x3 form: three persistent kernels, one block a compute unit
+int mfma_grid(int items) {
   int cus = 256;
   int dev = 0;
   if (hipGetDevice(&dev) == hipSuccess) {
@@ -759,22 +743,35 @@ int mfma_grid(dm_ctx* c, int items) {
         v > 0)
       cus = v;
   }
-  (void)c;
   return std::max(1, std::min(items, cus));
+}
+
+template <int M>
+void launch_mf_cols(dm_ctx* c) {
+  static_assert(M <= dmk::kMfMaxModes, "modes of this form");
+  const int nv = c->total_views;
+  hipLaunchKernelGGL(dmk::k_mf_cols<M>, dim3(mfma_grid(nv * dmk::kMfNt)),
+                     dim3(dmk::kMfThreads), 0, c->stream, c->scan_dev(), c->vmap(), nv, c->wf());
 }
 
 dm_status launch_views_mfma(dm_ctx* c) {
   const int M = c->M, nv = c->total_views;
-  hipLaunchKernelGGL(dmk::k_mf_rows_fwd, dim3(mfma_grid(c, nv * M)),
-                     dim3(dmk::kMfRowsThreads), kMfLdsW,
+  hipLaunchKernelGGL(dmk::k_mf_rows_fwd, dim3(mfma_grid(nv * M)), dim3(dmk::kMfThreads), 0,
                      c->stream, c->scan_dev(), c->vmap(), nv, M, c->wf());
   DM_LAUNCHED(c, "k_mf_rows_fwd");
-  hipLaunchKernelGGL(dmk::k_mf_cols, dim3(mfma_grid(c, nv * dmk::kMfNt)),
-                     dim3(dmk::kMfColsThreads), kMfLdsCols,
-                     c->stream, c->scan_dev(), c->vmap(), nv, M, c->wf());
+  switch (M) {
+    case 1: launch_mf_cols<1>(c); break;
+    case 2: launch_mf_cols<2>(c); break;
+    case 3: launch_mf_cols<3>(c); break;
+    case 4: launch_mf_cols<4>(c); break;
+    case 5: launch_mf_cols<5>(c); break;
+    case 6: launch_mf_cols<6>(c); break;
+    case 7: launch_mf_cols<7>(c); break;
+    case 8: launch_mf_cols<8>(c); break;
+    default: c->err = "the BF16x3 DFT form takes at most 8 modes"; return DM_E_UNSUPPORTED;
+  }
   DM_LAUNCHED(c, "k_mf_cols");
-  hipLaunchKernelGGL(dmk::k_mf_rows_inv, dim3(mfma_grid(c, nv)), dim3(dmk::kMfRowsThreads),
-                     kMfLdsW,
+  hipLaunchKernelGGL(dmk::k_mf_rows_inv, dim3(mfma_grid(2 * nv)), dim3(dmk::kMfThreads), 0,
                      c->stream, c->scan_dev(), c->vmap(), nv, M, c->wf());
   DM_LAUNCHED(c, "k_mf_rows_inv");
   return DM_OK;
@@ -1069,7 +1066,6 @@ dm_status batch_init(dm_ctx** out, int n_scans, const dm_desc* descs, const floa
     wtab = mfma_dft_table();
     INIT_HIP(hipMemcpyAsync(const_cast<uint4*>(c->wf()), wtab.data(), wtab.size() * sizeof(uint4),
                             hipMemcpyHostToDevice, c->stream));
-    INIT_HIP(set_mfma_lds());
   }
   INIT_HIP(hipMemcpyAsync(c->vmap(), vmap.data(), vmap.size() * sizeof(int2),
                           hipMemcpyHostToDevice, c->stream));

@@ -4,6 +4,7 @@ and the first size of a split)."""
 import pytest
 
 from paper_1808_10375_amd import synth
+import test_gpu_bf16x3 as bf16x3
 from test_gpu_parity import one_step_case, say
 
 pytestmark = pytest.mark.gpu
@@ -17,3 +18,13 @@ pytestmark = pytest.mark.gpu
 def test_probe_division_over_chunks_and_modes(seed, n, f, m):
     say(f"case probe division seed={seed} N={n} F={f} M={m}")
     one_step_case(synth.random_case(seed, n, f, m, 2 * f + 7, 2 * f + 3, perturb=0.5))
+
+
+# the column kernel of the BF16x3 form is compiled per mode count; the counts
+# the form's own tests leave out, with view counts that leave the persistent
+# blocks nothing (two views: fewer frames than blocks) or an uneven share
+@pytest.mark.parametrize("seed,n,m", [(91, 2, 2), (92, 41, 2), (93, 9, 4), (94, 7, 6),
+                                      (95, 6, 7)])
+def test_bf16x3_mode_counts(seed, n, m):
+    say(f"case bf16x3 modes seed={seed} N={n} M={m}")
+    bf16x3.compare(synth.random_case(seed, n, 128, m, 190, 200, perturb=0.3))
