@@ -118,40 +118,22 @@ int row_block(int F) {
   return F;
 }
 
+// complex values per frame of the spectrum buffer
+size_t spectrum_frame(int F) {
+  switch (F) {
+    case 188: return dmk::Mix<188>::FT;
+    case 200: return dmk::Mix<200>::FT;
+  }
+  return (size_t)F * F;
+}
+
 // row blocks per frame of the three-kernel path (one eps_psi partial each)
 int row_parts(int F) {
   switch (F) {
-    case 188: return dmk::Mix<188>::NBLK;
-    case 200: return dmk::Mix<200>::NBLK;
+    case 188: return dmk::Mix<188>::LB;
+    case 200: return dmk::Mix<200>::LB;
   }
   return F / row_block(F);
-}
-
-// threads per line of the mixed-radix transforms (Q + 1)
-int mix_qt(int F) { return F == 188 ? dmk::Mix<188>::QT : dmk::Mix<200>::QT; }
-
-// columns per block of the mixed-radix column kernel: a power of two up to
-// 16 with CB * M * (Q + 1) threads (rounded to whole waves) at most 512.
-// The kernel is bound by its arithmetic and barriers, and smaller blocks
-// overlap one block's barriers with another's work: at 10000 x 4 x 188^2
-// blocks of 384 threads (CB = 2) take 12.6 ms against 15.0 ms with 768
-// (CB = 4); with 192 (CB = 1) the view update is 1.3 ms slower again.
-int mix_cols_per_block(int F, int M) {
-  const int QT = mix_qt(F);
-  int p = 1;
-  while (p * 2 <= 16 && ((p * 2 * M * QT + 63) / 64) * 64 <= 512) p *= 2;
-  return p;
-}
-
-int mix_cols_threads(int F, int M, int cb) { return ((cb * M * mix_qt(F) + 63) / 64) * 64; }
-
-// dynamic LDS of the mixed-radix column kernel: cb * M exchange lines of
-// Q * R + 2 complex values, the mode powers [M][cb][F], the scale [cb][F]
-// and the twiddle tables (F + Q complex)
-size_t mix_cols_lds_bytes(int F, int M, int cb) {
-  const int Q = mix_qt(F) - 1;
-  return (size_t)cb * M * (F + 2) * sizeof(float2) + (size_t)(M + 1) * cb * F * sizeof(float) +
-         (size_t)(F + Q) * sizeof(float2);
 }
 
 // ---------------------------------------------------------------------------
@@ -190,7 +172,7 @@ ScanLayout scan_layout(const dm_desc& d) {
   L.psi = take(N * M * FF * c8);
   L.opart = take(N * NL * FF * c8);
   L.gscr = d.frame <= 128 ? take(N * FF * 4) : 0;
-  L.tspec = has_spectrum_buffer(d) ? take(N * M * FF * c8) : 0;
+  L.tspec = has_spectrum_buffer(d) ? take(N * M * spectrum_frame(d.frame) * c8) : 0;
   L.P = take(M * FF * c8);
   L.O = take(NL * d.obj_h * d.obj_w * c8);
   L.D = take(FF * 4);
@@ -514,6 +496,21 @@ hipError_t set_cols_lds(int F, int bytes) {
   return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
+// dynamic LDS of the mixed-radix kernels (one mode needs no more than 64 KB)
+template <int F>
+hipError_t set_mixed_lds(int M) {
+  if (M < 2) return hipSuccess;
+  const void* inv[2] = {reinterpret_cast<const void*>(dmk::k_mix_rows_inv<F, false, false>),
+                        reinterpret_cast<const void*>(dmk::k_mix_rows_inv<F, true, false>)};
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(dmk::k_mix_cols<F, false>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)dmk::mix_cols_lds<F>(M));
+  for (int k = 0; k < 2 && e == hipSuccess; ++k)
+    e = hipFuncSetAttribute(inv[k], hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)dmk::mix_inv_lds<F>(M));
+  return e;
+}
+
 // (Re)build everything that depends on the tuning: tile lists, chunking, the
 // scan descriptor table and the block maps; upload them.  Synchronises.
 dm_status apply_tuning(dm_ctx* c, const dm_tuning& t) {
@@ -588,10 +585,7 @@ dm_status apply_tuning(dm_ctx* c, const dm_tuning& t) {
   DM_HIP(c, hipMemcpyAsync(c->cmap(), cmap.data(), cmap.size() * sizeof(int2),
                            hipMemcpyHostToDevice, c->stream));
   if (t.view_path == DM_VIEWS_THREE_KERNEL && is_mixed(c->F)) {
-    const int lds = (int)mix_cols_lds_bytes(c->F, c->M, mix_cols_per_block(c->F, c->M));
-    const void* k = c->F == 188 ? reinterpret_cast<const void*>(dmk::k_mix_cols<188>)
-                                : reinterpret_cast<const void*>(dmk::k_mix_cols<200>);
-    DM_HIP(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    DM_HIP(c, c->F == 188 ? set_mixed_lds<188>(c->M) : set_mixed_lds<200>(c->M));
   } else if (t.view_path == DM_VIEWS_THREE_KERNEL) {
     const int MT = c->M * c->L;
     const int lds = (int)cols_lds_bytes(c->F, MT, cols_per_block(c->F, MT));
@@ -671,28 +665,35 @@ dm_status launch_views_multipass(dm_ctx* c, bool direct) {
   return DM_OK;
 }
 
-// Frames of edge F = R * Q (188, 200): the same three passes with the
+// Frames of edge F = 4 Q (188, 200): the same three passes with the
 // mixed-radix line transforms.
-template <int F>
-dm_status launch_views_mixed(dm_ctx* c, bool direct) {
+template <int F, bool ONE>
+dm_status launch_views_mixed_modes(dm_ctx* c, bool direct) {
   using C = dmk::Mix<F>;
-  const int M = c->M;
-  hipLaunchKernelGGL(dmk::k_mix_rows_fwd<F>, dim3(c->total_views, C::NBLK), dim3(C::NT), 0,
-                     c->stream, c->scan_dev(), c->vmap(), c->tw(), M);
+  const int M = c->M, blocks = c->total_views * C::LB;
+  hipLaunchKernelGGL(dmk::k_mix_rows_fwd<F>, dim3(blocks, M), dim3(64), 0, c->stream,
+                     c->scan_dev(), c->vmap(), c->tw(), M);
   DM_LAUNCHED(c, "k_mix_rows_fwd");
-  const int cb = mix_cols_per_block(F, M);
-  hipLaunchKernelGGL(dmk::k_mix_cols<F>, dim3(c->total_views * ((F + cb - 1) / cb)),
-                     dim3(mix_cols_threads(F, M, cb)), mix_cols_lds_bytes(F, M, cb), c->stream,
-                     c->scan_dev(), c->vmap(), c->tw(), M, cb, direct ? 1 : 0);
+  hipLaunchKernelGGL((dmk::k_mix_cols<F, ONE>), dim3(blocks),
+                     dim3(64 * dmk::mix_cols_waves(M)), dmk::mix_cols_lds<F>(M), c->stream,
+                     c->scan_dev(), c->vmap(), c->tw(), M, direct ? 1 : 0);
   DM_LAUNCHED(c, "k_mix_cols");
+  const dim3 bi(64 * std::min(M, dmk::kMixWaves));
+  const size_t li = dmk::mix_inv_lds<F>(M);
   if (direct)
-    hipLaunchKernelGGL(dmk::k_mix_rows_inv_direct<F>, dim3(c->total_views, C::NBLK),
-                       dim3(C::NT), 0, c->stream, c->scan_dev(), c->vmap(), c->tw(), M);
+    hipLaunchKernelGGL((dmk::k_mix_rows_inv<F, true, ONE>), dim3(blocks), bi, li, c->stream,
+                       c->scan_dev(), c->vmap(), c->tw(), M);
   else
-    hipLaunchKernelGGL(dmk::k_mix_rows_inv<F>, dim3(c->total_views, C::NBLK), dim3(C::NT), 0,
-                       c->stream, c->scan_dev(), c->vmap(), c->tw(), M);
+    hipLaunchKernelGGL((dmk::k_mix_rows_inv<F, false, ONE>), dim3(blocks), bi, li, c->stream,
+                       c->scan_dev(), c->vmap(), c->tw(), M);
   DM_LAUNCHED(c, "k_mix_rows_inv");
   return DM_OK;
+}
+
+template <int F>
+dm_status launch_views_mixed(dm_ctx* c, bool direct) {
+  return c->M == 1 ? launch_views_mixed_modes<F, true>(c, direct)
+                   : launch_views_mixed_modes<F, false>(c, direct);
 }
 
 // The split DFT matrix in B-fragment order (see dm_mfma.hpp): W[a][b] =

@@ -1,302 +1,466 @@
 // dm_mixed.hpp -- the view update (Eq. 3 with F_c, Section II) for frames
-// whose edge is not a power of two: F = R * Q with R a power of two and Q
-// odd (188 = 4 * 47, 200 = 8 * 25, the frame sizes the paper's own
-// measurements use).  Three kernels around the spectrum buffer, as for F =
-// 256: row DFTs, then column DFTs with the mode sum and modulus scale and the
-// inverse column DFTs, then inverse row DFTs with the update.
+// whose edge is not a power of two: F = 4 Q (188 = 4 * 47, 200 = 4 * 50, the
+// frame sizes the paper's own measurements use).  Three kernels around the
+// spectrum buffer, as for F = 256: row DFTs, then column DFTs with the mode
+// sum and modulus scale and the inverse column DFTs, then inverse row DFTs
+// with the update.
 //
-// One length-F line is transformed with one level of the Cooley-Tukey split
-// n = Q n1 + n2, k = k1 + R k2:
-//   X[k1 + R k2] = sum_{n2} W_Q^{n2 k2} W_F^{n2 k1} sum_{n1} x[Q n1 + n2] W_R^{n1 k1}
-// by Q + 1 threads.  Thread n2 < Q holds x[Q n1 + n2] (n1 < R) in registers,
-// does the R-point DFT there, applies W_F^{n2 k1} and writes its R values to
-// row n2 of the line's LDS buffer.  The Q-point DFTs over the rows use the
-// symmetry of W_Q for odd Q: with u_n = y_n + y_{Q-n} and v_n = y_n - y_{Q-n}
-// (formed in place, 1 <= n <= (Q-1)/2) and c_n + i s_n = W_Q^{n p},
-//   Y_p     = y_0 + sum_n c_n u_n + i sum_n s_n v_n,
-//   Y_{Q-p} = y_0 + sum_n c_n u_n - i sum_n s_n v_n,
-// so thread t forms the two real-weighted sums for p = t / 2 over half of the
-// k1 range (half t % 2) and gets both outputs: a quarter of the products of
-// the direct sum, and each LDS row read serves two outputs.  The inverse runs
-// the same steps with conjugate twiddles and one more exchange, so values
-// return to the thread and register they came from.  Q-point twiddles come
-// from a table in LDS every eighth step and by one complex product with
-// W_Q^p in between.
+// A wave transforms 16 lines in registers, without LDS or barriers: lane
+// (n2 = lane / 16, line = lane % 16) holds x[4 n1 + n2], n1 < Q, and with
+// n = 4 n1 + n2, k = k1 + Q k2
+//   X[k1 + Q k2] = sum_{n2} W_4^{n2 k2} W_F^{n2 k1} sum_{n1} x[4 n1 + n2] W_Q^{n1 k1}.
+// The Q-point DFTs run in the lane.  Q = 47 uses the symmetry of W_Q for odd Q:
+// with u_n = x_n + x_{Q-n}, v_n = x_n - x_{Q-n} and c_n + i s_n = W_Q^{n p},
+//   Y_p     = x_0 + sum_n c_n u_n + i sum_n s_n v_n,
+//   Y_{Q-p} = x_0 + sum_n c_n u_n - i sum_n s_n v_n
+// (a quarter of the products of the direct sum, every factor a literal of an
+// unrolled FMA).  Q = 50 is 2 x 5 x 5 in place.  Both give their outputs in
+// pairs A = Y[kA], B = Y[kB]; the four-point DFT over n2 crosses the lanes of
+// a line, two values at a time: v_permlane32_swap gives the lower half-wave
+// both halves' A and the upper one both B, v_permlane16_swap then does the
+// same with sums and differences, so that lane (h = lane / 32, b = lane / 16 %
+// 2) ends with X[k + Q b] and X[k + Q (b + 2)], k = h ? kB : kA.  The inverse
+// runs the same steps backwards and returns values to the lane they came
+// from.
+//
+// The spectrum buffer is k-major, T[kx][row], its lines padded to whole blocks
+// of 16 rows: the row kernels touch it in runs of 16 rows, exactly one 128-byte
+// cache line each (unpadded, a run met two lines that other XCDs wrote too),
+// the column kernel along its lines, 32 bytes a line and instruction.
+//
+// What bounds it: moving the spectra and the views, at 60-75% of a copy's rate,
+// and at 188^2 also the products of the 47-point DFTs (2116 FMAs a lane, 45 a
+// value and dimension).  At 1500 x 4 x 188^2 rows, columns and inverse rows take
+// 0.85, 1.20 and 1.29 ms, at 2521 x 1 x 200^2 0.41, 0.51 and 0.68 ms.  The form
+// before kept the lines in LDS with Q + 1 threads a line, each reading 32 bytes
+// of LDS per 8 FMAs between four barriers a transform: 0.91, 2.07, 1.27 ms and
+// 0.54, 0.86, 0.86 ms.  The row kernels stream the views and the spectra past
+// the caches (non-temporal: inverse rows 0.77 -> 0.68 ms at 200^2), which holds
+// the probe and object in them; the column kernel does not (1.23 against 1.20
+// ms at 188^2).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <float.h>
+
+#include <type_traits>
 
 #include "dm_kernels.hpp"
 
 namespace dmk {
 
 template <int F>
-struct MixCfg;
+struct Mix;
 template <>
-struct MixCfg<188> {
-  static constexpr int R = 4, Q = 47;
+struct Mix<188> {
+  static constexpr int Q = 47, NP = 24, LB = 12;  // pairs, blocks of 16 lines
+  static constexpr int LDT = 16 * LB, FT = 188 * LDT;  // spectrum line, frame (complex)
+  static constexpr int kB(int i) { return 47 - i; }
+  static constexpr bool hasB(int i) { return i > 0; }
 };
 template <>
-struct MixCfg<200> {
-  static constexpr int R = 8, Q = 25;
+struct Mix<200> {
+  static constexpr int Q = 50, NP = 25, LB = 13;
+  static constexpr int LDT = 16 * LB, FT = 200 * LDT;
+  static constexpr int kB(int i) { return 25 + i; }
+  static constexpr bool hasB(int) { return true; }
 };
 
-template <int F>
-struct Mix {
-  static constexpr int R = MixCfg<F>::R, Q = MixCfg<F>::Q;
-  static constexpr int QT = Q + 1;         // threads per line
-  static constexpr int H = R / 2;         // k1 values per pair thread
-  static constexpr int NP = (Q - 1) / 2;  // symmetric pairs of rows
-  static constexpr int LS = Q * R + 2;    // LDS line stride (complex)
-  static constexpr int RB = 256 / QT;     // rows per block of the row kernels
-  static constexpr int NT = (RB * QT + 63) / 64 * 64;  // whole waves
-  static constexpr int NBLK = (F + RB - 1) / RB;      // row blocks per frame
+// f(integral_constant<int, B>) ... f(integral_constant<int, E - 1>)
+template <int B, int E, class Fn>
+__device__ __forceinline__ void static_for(Fn&& f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
+  }
+}
+
+// Holds a value at this point of the program: the code that forms it stays
+// before, and so do the registers of its operands.  Without, the compiler
+// forms the values of a long unrolled block where they are first used, keeps
+// every load alive until then and spills.
+__device__ __forceinline__ void pin(float2& a) { asm volatile("" : "+v"(a.x), "+v"(a.y)); }
+
+// cos and sin of 2 pi m / N in double at compile time (Taylor series of the
+// angle reduced to an eighth turn)
+struct CosSin {
+  double c, s;
+};
+constexpr CosSin cos_sin_turn(int m, int n) {
+  m %= n;
+  if (m < 0) m += n;
+  // octant: angle = 2 pi (8 m mod n ... ) folded to [0, pi/4]
+  int o = (8 * m) / n;       // 0 .. 7
+  const int r = 8 * m - o * n;  // remainder in eighth turns, r / n in [0, 1)
+  const bool flip = o & 1;   // mirror odd octants at their end
+  const double t = (flip ? (double)(n - r) : (double)r) / n;
+  const double x = t * 0.78539816339744830961566084581988;  // pi / 4
+  const double x2 = x * x;
+  double c = 1.0, s = x, tc = 1.0, ts = x;
+  for (int k = 1; k < 14; ++k) {
+    tc *= -x2 / ((2 * k - 1) * (2 * k));
+    ts *= -x2 / ((2 * k) * (2 * k + 1));
+    c += tc;
+    s += ts;
+  }
+  if (flip) ++o;  // angle = o pi / 4 - x
+  const double h = 0.70710678118654752440084436210485;
+  double oc = 0, os = 0;
+  switch (o & 7) {
+    case 0: oc = 1; os = 0; break;
+    case 1: oc = h; os = h; break;
+    case 2: oc = 0; os = 1; break;
+    case 3: oc = -h; os = h; break;
+    case 4: oc = -1; os = 0; break;
+    case 5: oc = -h; os = -h; break;
+    case 6: oc = 0; os = -1; break;
+    default: oc = h; os = -h; break;
+  }
+  const double sx = flip ? -s : s;
+  return CosSin{oc * c - os * sx, os * c + oc * sx};
+}
+
+// a * exp(DIR 2 pi i M / N)
+template <int DIR, int M, int N>
+__device__ __forceinline__ float2 mix_tw(float2 a) {
+  constexpr CosSin w = cos_sin_turn(M, N);
+  constexpr float c = (float)w.c, s = (float)(DIR * w.s);
+  return make_float2(a.x * c - a.y * s, a.x * s + a.y * c);
+}
+
+template <int DIR>
+__device__ __forceinline__ void dft5(float2& a0, float2& a1, float2& a2, float2& a3, float2& a4) {
+  constexpr CosSin w1 = cos_sin_turn(1, 5), w2 = cos_sin_turn(2, 5);
+  constexpr float c1 = (float)w1.c, c2 = (float)w2.c;
+  constexpr float s1 = (float)(DIR * w1.s), s2 = (float)(DIR * w2.s);
+  const float2 t1 = cadd(a1, a4), t2 = cadd(a2, a3), t3 = csub(a1, a4), t4 = csub(a2, a3);
+  const float2 b1 = make_float2(a0.x + c1 * t1.x + c2 * t2.x, a0.y + c1 * t1.y + c2 * t2.y);
+  const float2 b2 = make_float2(a0.x + c2 * t1.x + c1 * t2.x, a0.y + c2 * t1.y + c1 * t2.y);
+  const float2 d1 = make_float2(s1 * t3.x + s2 * t4.x, s1 * t3.y + s2 * t4.y);
+  const float2 d2 = make_float2(s2 * t3.x - s1 * t4.x, s2 * t3.y - s1 * t4.y);
+  a0 = cadd(a0, cadd(t1, t2));
+  a1 = make_float2(b1.x - d1.y, b1.y + d1.x);
+  a4 = make_float2(b1.x + d1.y, b1.y - d1.x);
+  a2 = make_float2(b2.x - d2.y, b2.y + d2.x);
+  a3 = make_float2(b2.x + d2.y, b2.y - d2.x);
+}
+
+// 25-point DFT of a[S i + S0], i < 25; output k is left at index
+// S (5 (k % 5) + k / 5) + S0
+template <int DIR, int S, int S0, int N>
+__device__ __forceinline__ void dft25(float2 (&a)[N]) {
+  static_for<0, 5>([&](auto i2) {
+    constexpr int o = S * i2 + S0;
+    dft5<DIR>(a[o], a[o + 5 * S], a[o + 10 * S], a[o + 15 * S], a[o + 20 * S]);
+    static_for<1, 5>([&](auto k1) {
+      a[o + 5 * S * k1] = mix_tw<DIR, i2 * k1, 25>(a[o + 5 * S * k1]);
+    });
+  });
+  // a[S (5 k1 + i2) + S0] = y_{i2}[k1]: over i2 for each k1
+  static_for<0, 5>([&](auto k1) {
+    constexpr int o = S * 5 * k1 + S0;
+    dft5<DIR>(a[o], a[o + S], a[o + 2 * S], a[o + 3 * S], a[o + 4 * S]);
+  });
+}
+// index i < 25 at which output k of dft25 is left
+constexpr int pos25(int k) { return 5 * (k % 5) + k / 5; }
+
+// sum over the pairs u, v of output p (and Q - p) of the 47-point DFT:
+// a[0] = x_0, a[n] = u_n, a[47 - n] = v_n for 1 <= n <= 23
+template <int DIR, int P>
+__device__ __forceinline__ void out47(const float2 (&a)[47], float2& A, float2& B) {
+  float2 su = a[0];
+  if constexpr (P == 0) {
+    static_for<1, 24>([&](auto n) { su = cadd(su, a[n]); });
+    A = su;
+    B = make_float2(0.f, 0.f);
+  } else {
+    float2 sv = make_float2(0.f, 0.f);
+    static_for<1, 24>([&](auto n) {
+      constexpr CosSin w = cos_sin_turn(n * P, 47);
+      constexpr float c = (float)w.c, s = (float)(DIR * w.s);
+      su.x += c * a[n].x;
+      su.y += c * a[n].y;
+      sv.x += s * a[47 - n].x;
+      sv.y += s * a[47 - n].y;
+    });
+    A = make_float2(su.x - sv.y, su.y + sv.x);
+    B = make_float2(su.x + sv.y, su.y - sv.x);
+  }
+}
+
+// exchanges of two values between the half-waves (v0's upper half with v1's
+// lower half) and between the rows of 16 lanes (v0's odd rows with v1's even)
+__device__ __forceinline__ void swap_halves(float& v0, float& v1) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v1), false,
+                                                  false);
+  v0 = __uint_as_float(r[0]);
+  v1 = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap_rows(float& v0, float& v1) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v0), __float_as_uint(v1), false,
+                                                  false);
+  v0 = __uint_as_float(r[0]);
+  v1 = __uint_as_float(r[1]);
+}
+
+// What a lane knows of its place: line of the wave, n2 = 2 h + b
+struct MixLane {
+  int line, n2, h, b;
+  __device__ __forceinline__ explicit MixLane(int lane)
+      : line(lane & 15), n2(lane >> 4), h(lane >> 5), b((lane >> 4) & 1) {}
 };
 
-// LDS tables: twl[m] = W_F^m = exp(-2 pi i m / F), m < F; twq[m] = W_Q^m.
+// Twiddles W_F^{n2 k1} in LDS, [k1][n2]
 template <int F>
-__device__ __forceinline__ void mix_load_tables(const float2* __restrict__ tw, float2* twl,
-                                                float2* twq, int t, int nt) {
-  constexpr int R = Mix<F>::R, Q = Mix<F>::Q;
-  for (int i = t; i < F; i += nt) twl[i] = tw[i];
-  for (int i = t; i < Q; i += nt) twq[i] = tw[R * i];
-}
-
-// Thread n < Q of a line: R-point DFT of its registers, twiddle W_F^{DIR n k1},
-// row n of the line buffer.
-template <int F, int DIR>
-__device__ __forceinline__ void mix_first(float2 (&a)[Mix<F>::R], float2* line,
-                                          const float2* twl, int n) {
-  constexpr int R = Mix<F>::R;
-  dftB<DIR, R>(a);
-#pragma unroll
-  for (int k1 = 1; k1 < R; ++k1) {
-    float2 w = twl[n * k1];
-    if constexpr (DIR > 0) w.y = -w.y;
-    a[k1] = cmul(a[k1], w);
-  }
-  float4* d = reinterpret_cast<float4*>(line + n * R);
-#pragma unroll
-  for (int h = 0; h < R / 2; ++h)
-    d[h] = make_float4(a[2 * h].x, a[2 * h].y, a[2 * h + 1].x, a[2 * h + 1].y);
-}
-
-// Rows n and Q - n (1 <= n <= (Q-1)/2, thread n of the line) become their
-// sum and difference, in place.
-template <int F>
-__device__ __forceinline__ void mix_uv(float2* line, int n) {
-  constexpr int R = Mix<F>::R, NP = Mix<F>::NP, Q = Mix<F>::Q;
-  if (n < 1 || n > NP) return;
-  float4* a = reinterpret_cast<float4*>(line + n * R);
-  float4* b = reinterpret_cast<float4*>(line + (Q - n) * R);
-#pragma unroll
-  for (int h = 0; h < R / 2; ++h) {
-    const float4 x = a[h], y = b[h];
-    a[h] = make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
-    b[h] = make_float4(x.x - y.x, x.y - y.y, x.z - y.z, x.w - y.w);
-  }
-}
-
-// Positions (k1 + R k2) of a thread's pair outputs: lo = Y_p, hi = Y_{Q-p},
-// H consecutive values each; p = 0 has no hi.
-template <int F>
-__device__ __forceinline__ void mix_pair_pos(int t, int& ilo, int& ihi) {
-  constexpr int R = Mix<F>::R, Q = Mix<F>::Q, H = Mix<F>::H;
-  const int p = t >> 1, h = t & 1;
-  ilo = h * H + R * p;
-  ihi = p > 0 ? h * H + R * (Q - p) : -1;
-}
-
-// Q-point DFTs over the rows (after mix_uv), thread t of the line:
-// lo[k] = Y_p[k1], hi[k] = Y_{Q-p}[k1] with p = t / 2, k1 = (t % 2) H + k.
-template <int F, int DIR>
-__device__ __forceinline__ void mix_pairs(float2 (&lo)[Mix<F>::H], float2 (&hi)[Mix<F>::H],
-                                          const float2* line, const float2* twq, int t) {
-  constexpr int R = Mix<F>::R, Q = Mix<F>::Q, H = Mix<F>::H, NP = Mix<F>::NP;
-  const int p = t >> 1, h = t & 1;
-  float2 su[H], sv[H];
-#pragma unroll
-  for (int k = 0; k < H; ++k) { su[k] = make_float2(0.f, 0.f); sv[k] = make_float2(0.f, 0.f); }
-  float2 step = twq[p];
-  if constexpr (DIR > 0) step.y = -step.y;
-  int idx = p;  // (n p) mod Q at the start of each group of eight
-#pragma unroll 1
-  for (int n0 = 1; n0 <= NP; n0 += 8) {
-    float2 w = twq[idx];
-    if constexpr (DIR > 0) w.y = -w.y;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const int n = n0 + s;
-      if (n <= NP) {
-        const float2* u = line + n * R + h * H;
-        const float2* v = line + (Q - n) * R + h * H;
-        float2 uu[H], vv[H];
-#pragma unroll
-        for (int k = 0; k < H; k += 2) {
-          const float4 a = *reinterpret_cast<const float4*>(u + k);
-          const float4 b = *reinterpret_cast<const float4*>(v + k);
-          uu[k] = make_float2(a.x, a.y); uu[k + 1] = make_float2(a.z, a.w);
-          vv[k] = make_float2(b.x, b.y); vv[k + 1] = make_float2(b.z, b.w);
-        }
-#pragma unroll
-        for (int k = 0; k < H; ++k) {
-          su[k].x += w.x * uu[k].x; su[k].y += w.x * uu[k].y;
-          sv[k].x += w.y * vv[k].x; sv[k].y += w.y * vv[k].y;
-        }
-        w = cmul(w, step);
-      }
-    }
-    idx += 8 * p;
-    idx %= Q;
-  }
-  const float2* y0 = line + h * H;
-#pragma unroll
-  for (int k = 0; k < H; ++k) {
-    const float2 a = make_float2(y0[k].x + su[k].x, y0[k].y + su[k].y);
-    lo[k] = make_float2(a.x - sv[k].y, a.y + sv[k].x);
-    hi[k] = make_float2(a.x + sv[k].y, a.y - sv[k].x);
-  }
-}
-
-// a thread's pair values to their rows of the line buffer
-template <int F>
-__device__ __forceinline__ void mix_put_pairs(float2* line, const float2 (&lo)[Mix<F>::H],
-                                              const float2 (&hi)[Mix<F>::H], int t) {
-  constexpr int H = Mix<F>::H;
-  int ilo, ihi;
-  mix_pair_pos<F>(t, ilo, ihi);
-#pragma unroll
-  for (int k = 0; k < H; k += 2) {
-    *reinterpret_cast<float4*>(line + ilo + k) =
-        make_float4(lo[k].x, lo[k].y, lo[k + 1].x, lo[k + 1].y);
-    if (ihi >= 0)
-      *reinterpret_cast<float4*>(line + ihi + k) =
-          make_float4(hi[k].x, hi[k].y, hi[k + 1].x, hi[k + 1].y);
-  }
-}
-
-// Thread n < Q after the inverse Q-point DFTs are back in the rows: row n,
-// twiddle W_F^{-n k1}, inverse R-point DFT; a[n1] = x[Q n1 + n].
-template <int F>
-__device__ __forceinline__ void mix_last_inv(float2 (&a)[Mix<F>::R], const float2* line,
-                                             const float2* twl, int n) {
-  constexpr int R = Mix<F>::R;
-  const float4* r = reinterpret_cast<const float4*>(line + n * R);
-#pragma unroll
-  for (int h = 0; h < R / 2; ++h) {
-    const float4 v = r[h];
-    a[2 * h] = make_float2(v.x, v.y);
-    a[2 * h + 1] = make_float2(v.z, v.w);
-  }
-#pragma unroll
-  for (int k1 = 1; k1 < R; ++k1) {
-    float2 w = twl[n * k1];
-    w.y = -w.y;
-    a[k1] = cmul(a[k1], w);
-  }
-  dftB<1, R>(a);
-}
-
-// Inverse line transform of the rows already in `line` (row k2 holds
-// X[k1 + R k2]); the caller synchronised after writing them.  Thread n < Q
-// of the line ends with a[n1] = x[Q n1 + n] (unnormalised).  Four barriers.
-template <int F>
-__device__ __forceinline__ void mix_inverse(float2 (&a)[Mix<F>::R], float2* line,
-                                            const float2* twl, const float2* twq, int t,
-                                            bool active) {
-  constexpr int H = Mix<F>::H, Q = Mix<F>::Q;
-  if (active) mix_uv<F>(line, t);
+__device__ __forceinline__ void mix_load_twiddles(const float2* __restrict__ tw, float2* twl,
+                                                  int t, int nt) {
+  constexpr int Q = Mix<F>::Q;
+  for (int i = t; i < 4 * Q; i += nt) twl[i] = tw[(i >> 2) * (i & 3)];
   __syncthreads();
-  float2 lo[H], hi[H];
-  if (active) mix_pairs<F, 1>(lo, hi, line, twq, t);
-  __syncthreads();
-  if (active) mix_put_pairs<F>(line, lo, hi, t);
-  __syncthreads();
-  if (active && t < Q) mix_last_inv<F>(a, line, twl, t);
 }
 
-// (1) Z = 2 P O - psi and the DFT along rows; RB rows of every mode of one
-// view per block, Q + 1 threads per row, mode after mode with the next
-// mode's psi in flight (the tables are loaded once per block).
-template <int F>
-__global__ __launch_bounds__(Mix<F>::NT) void k_mix_rows_fwd(
-    const ScanDev* __restrict__ scans, const int2* __restrict__ vmap,
-    const float2* __restrict__ tw, int M) {
+// DFT4 over n2 of the pair (A, B): X[b], X[b + 2] of the lane's k1
+__device__ __forceinline__ void cross_fwd(float2 A, float2 B, int b, float2& x0, float2& x1) {
+  swap_halves(A.x, B.x);
+  swap_halves(A.y, B.y);
+  float2 s = cadd(A, B), d = csub(A, B);
+  swap_rows(s.x, d.x);
+  swap_rows(s.y, d.y);
+  // rows b = 1 hold d_0, d_1: X_1 = d_0 - i d_1, X_3 = d_0 + i d_1
+  const float2 e = make_float2(b ? d.y : d.x, b ? -d.x : d.y);
+  x0 = cadd(s, e);
+  x1 = csub(s, e);
+}
+// its inverse (unnormalised)
+__device__ __forceinline__ void cross_inv(float2 x0, float2 x1, int b, float2& A, float2& B) {
+  float2 e = cadd(x0, x1), o = csub(x0, x1);
+  // rows b = 1: o_1 = X_1 - X_3 enters z_1, z_3 as +- i o_1
+  o = make_float2(b ? -o.y : o.x, b ? o.x : o.y);
+  swap_rows(e.x, o.x);
+  swap_rows(e.y, o.y);
+  A = cadd(e, o);
+  B = csub(e, o);
+  swap_halves(A.x, B.x);
+  swap_halves(A.y, B.y);
+}
+
+// Forward transform of the wave's lines, a[n1] = x[4 n1 + n2];
+// emit(integral_constant i, X0, X1) gets X[k + Q b] and X[k + Q (b + 2)], k = kA = i or
+// kB(i) by half-wave (where the upper half has none, its values are 0).
+template <int F, class Emit>
+__device__ __forceinline__ void mix_fwd(float2 (&a)[Mix<F>::Q], const float2* twl,
+                                        const MixLane& ln, Emit&& emit) {
   using C = Mix<F>;
-  constexpr int R = C::R, Q = C::Q, QT = C::QT, H = C::H, RB = C::RB, LS = C::LS, FF = F * F;
-  __shared__ __align__(16) float2 xb[RB * LS];
-  __shared__ float2 twl[F];
-  __shared__ float2 twq[Q];
-  const int t = threadIdx.x;
-  const int2 vm = vmap[blockIdx.x];
-  const ScanDev& sc = scans[vm.x];
-  const int j = uni(vm.y);
-  const int rl = t / QT, tl = t % QT;
-  const int row = blockIdx.y * RB + rl;
-  const bool active = rl < RB && row < F;
-  const bool owner = active && tl < Q;
-  float2* line = xb + rl * LS;
-  mix_load_tables<F>(tw, twl, twq, t, C::NT);
-  const int W = uni(sc.W);
-  const int y0 = uni(kidx(sc.pos)[2 * j]), x0 = uni(kidx(sc.pos)[2 * j + 1]);
-  const float2* __restrict__ p0 = sc.psi + (size_t)j * M * FF + (size_t)row * F;
-  const float2* __restrict__ Or = sc.O + (size_t)(y0 + row) * W + x0;
-  // at R = 4 the object row values are held across the modes (188^2 x 4
-  // modes: 27.9 -> 27.6 ms for the view update); at R = 8 holding them
-  // costs a wave per SIMD and was slower
-  constexpr bool kHoldO = R <= 4;
-  float2 psn[R], ov[R];
-  if (owner) {
-#pragma unroll
-    for (int n1 = 0; n1 < R; ++n1) {
-      psn[n1] = p0[Q * n1 + tl];
-      if constexpr (kHoldO) ov[n1] = Or[Q * n1 + tl];
-    }
+  if constexpr (F == 188) {
+    static_for<1, 24>([&](auto n) {
+      const float2 x = a[n], y = a[47 - n];
+      a[n] = cadd(x, y);
+      a[47 - n] = csub(x, y);
+    });
+  } else {
+    dft25<-1, 2, 0>(a);
+    dft25<-1, 2, 1>(a);
   }
-  for (int m = 0; m < M; ++m) {
-    const int jm = j * M + m;
-    float2 a[R] = {};
-    if (owner) {
-      const float2* __restrict__ Pm = sc.P + (size_t)m * FF + (size_t)row * F;
-#pragma unroll
-      for (int n1 = 0; n1 < R; ++n1) {
-        const int v = Q * n1 + tl;
-        const float2 phi = cmul(Pm[v], kHoldO ? ov[n1] : Or[v]);
-        a[n1] = make_float2(2.f * phi.x - psn[n1].x, 2.f * phi.y - psn[n1].y);
-      }
-      if (m + 1 < M) {
-        const float2* __restrict__ pq = p0 + (size_t)(m + 1) * FF;
-#pragma unroll
-        for (int n1 = 0; n1 < R; ++n1) psn[n1] = pq[Q * n1 + tl];
-      }
+  static_for<0, C::NP>([&](auto i) {
+    float2 A, B;
+    if constexpr (F == 188) {
+      out47<-1, i>(a, A, B);
+    } else {
+      constexpr int p = 2 * pos25(i);
+      const float2 o = mix_tw<-1, i, 50>(a[p + 1]);
+      A = cadd(a[p], o);
+      B = csub(a[p], o);
     }
-    __syncthreads();  // tables; the previous mode's reads of the lines are done
-    if (owner) mix_first<F, -1>(a, line, twl, tl);
-    __syncthreads();
-    if (active) mix_uv<F>(line, tl);
-    __syncthreads();
-    if (active) {
-      float2 lo[H], hi[H];
-      mix_pairs<F, -1>(lo, hi, line, twq, tl);
-      int ilo, ihi;
-      mix_pair_pos<F>(tl, ilo, ihi);
-      float2* __restrict__ Tr = sc.tspec + (size_t)jm * FF + (size_t)row * F;
-#pragma unroll
-      for (int k = 0; k < H; ++k) {
-        Tr[ilo + k] = lo[k];
-        if (ihi >= 0) Tr[ihi + k] = hi[k];
+    if constexpr (i > 0) A = cmul(A, twl[i * 4 + ln.n2]);
+    if constexpr (C::hasB(i)) B = cmul(B, twl[C::kB(i) * 4 + ln.n2]);
+    float2 x0, x1;
+    cross_fwd(A, B, ln.b, x0, x1);
+    emit(i, x0, x1);
+    __builtin_amdgcn_sched_barrier(0);
+  });
+}
+
+// Inverse, first part: x[2 i], x[2 i + 1] = the X0, X1 of mix_fwd -> a, what
+// mix_inv_out forms the outputs from.
+template <int F>
+__device__ __forceinline__ void mix_inv_in(const float2 (&x)[2 * Mix<F>::NP],
+                                           float2 (&a)[Mix<F>::Q], const float2* twl,
+                                           const MixLane& ln) {
+  using C = Mix<F>;
+  static_for<0, C::NP>([&](auto i) {
+    float2 A, B;
+    cross_inv(x[2 * i], x[2 * i + 1], ln.b, A, B);
+    auto conj_tw = [&](float2 z, int k) {
+      const float2 w = twl[k * 4 + ln.n2];
+      return make_float2(z.x * w.x + z.y * w.y, z.y * w.x - z.x * w.y);
+    };
+    if constexpr (i > 0) A = conj_tw(A, i);
+    if constexpr (C::hasB(i)) B = conj_tw(B, C::kB(i));
+    if constexpr (F == 188) {
+      if constexpr (i == 0) {
+        a[0] = A;
+      } else {
+        a[i] = cadd(A, B);
+        a[47 - i] = csub(A, B);
       }
+      if constexpr (i > 0) pin(a[47 - i]);
+      pin(a[i]);
+    } else {
+      a[2 * i] = cadd(A, B);
+      a[2 * i + 1] = mix_tw<1, i, 50>(csub(A, B));
+      pin(a[2 * i]);
+      pin(a[2 * i + 1]);
     }
+    __builtin_amdgcn_sched_barrier(0);
+  });
+  if constexpr (F == 200) {
+    dft25<1, 2, 0>(a);
+    dft25<1, 2, 1>(a);
+  }
+}
+// Second part: outputs come in NP groups of two (one in group 0 at 188);
+// mix_n(i, e) is the n1 of output e of group i, mix_inv_out gives both.
+template <int F>
+constexpr int mix_n(int i, int e) {
+  return F == 188 ? (e ? 47 - i : i) : 2 * i + e;
+}
+template <int F, int I>
+__device__ __forceinline__ void mix_inv_out(const float2 (&a)[Mix<F>::Q], float2 (&z)[2]) {
+  if constexpr (F == 188) {
+    out47<1, I>(a, z[0], z[1]);
+  } else {
+    z[0] = a[2 * pos25(I)];
+    z[1] = a[2 * pos25(I) + 1];
   }
 }
 
-// Slot (view * nblk + column block) of block b when every column block of a
-// view runs on one XCD: the dispatcher sends block b to XCD b % 8, so XCD x
-// takes the views v = x, x + 8, ... whole, one after the other.  A row of an
-// F = 188 or 200 frame is not a multiple of 128 bytes, so column strips of
-// one view share cache lines across their edges; on one XCD those lines are
-// fetched into its L2 once.  Bijective on whole groups of 8 views; the
-// remaining blocks keep their index.
+// byte offset that every buffer drops (and offsets within a frame of it)
+constexpr int kMixOob = 0x40000000;
+
+// Byte offset of X0 of pair i in a k-major frame; X1 is 2 Q lines further.  Rows
+// past the frame hold zeros in the padding.
+template <int F>
+struct MixSpec {
+  int base, step;
+  __device__ __forceinline__ MixSpec(const MixLane& ln, int line) {
+    using C = Mix<F>;
+    base = (((ln.h ? C::kB(0) : 0) + C::Q * ln.b) * C::LDT + line) * 8;
+    step = (F == 188 && ln.h) ? -C::LDT * 8 : C::LDT * 8;
+  }
+  __device__ __forceinline__ int at(int i, const MixLane& ln) const {
+    return (F == 188 && i == 0 && ln.h) ? kMixOob : base + i * step;
+  }
+  static constexpr int kX1 = 2 * Mix<F>::Q * Mix<F>::LDT * 8;
+};
+
+// Lines pass between memory and the lanes in chunks of CW values through a
+// wave's own LDS tile of its 16 lines: an instruction then moves 64 / CW lines x
+// CW consecutive values instead of 16 lines x 32 bytes (reading x[4 n1 + n2]
+// straight from memory the row kernels took 1.47 and 2.43 ms at 1500 x 4 x
+// 188^2).  The row kernels take 64 values (512 bytes) a line; the column
+// kernel, whose tiles have to fit its waves' slots of LDS, 32.  Tile lines are
+// CW + 4 values apart: the lanes' reads of x[4 n1 + n2] then cover all banks.
+constexpr int kRowCW = 64, kColCW = 32;
+template <int CW>
+constexpr int kMixTile = 16 * (CW + 4);  // float2 per tile
+template <int F, int CW>
+constexpr int kMixChunks = (F + CW - 1) / CW;
+
+// Element (i, lane) of chunk CH, i < kI: with L = 64 / (values used of a
+// line) lines an instruction, line L i + lane / (64 / L) of the wave's, value
+// CW CH + lane % (64 / L).  (200 leaves a last chunk of 8 values: eight lines an
+// instruction.)  Lines past the frame load its last ones again and store
+// nothing; values past the line load 0 and store nothing.  A dropped access
+// gets a lane offset out of range and a scalar offset within it (the range
+// check subtracts the scalar offset).
+template <int F, int CW, int CH>
+struct MixIO {
+  static constexpr int kWidth = F - CW * CH < CW ? F - CW * CH : CW;
+  static constexpr int kSpan = kWidth <= 8 ? 8 : CW;  // lanes a line
+  static constexpr int L = 64 / kSpan, kI = 16 / L;
+  static_assert(F % L == 0 && 16 % L == 0, "the lines of an instruction are in the frame together");
+  // per-lane byte offset in lines of `stride` values
+  __device__ __forceinline__ static int load_off(int lane, int stride) {
+    const int v = lane % kSpan;
+    return v < kWidth ? ((lane / kSpan) * stride + v) * 8 : kMixOob;
+  }
+  __device__ __forceinline__ static bool in(int lane, int line0, int i) {
+    return line0 + L * i < F && (kWidth == kSpan || lane % kSpan < kWidth);
+  }
+  __device__ __forceinline__ static int store_off(int lane, int stride, int line0, int i) {
+    return in(lane, line0, i) ? ((lane / kSpan) * stride + lane % kSpan) * 8 : kMixOob;
+  }
+  // scalar offset; base: the wave's first line
+  __device__ __forceinline__ static int s(int i, int line0, int stride, int base) {
+    return base + min(L * i, F - L - line0) * stride * 8 + CW * CH * 8;
+  }
+  __device__ __forceinline__ static int tile(int lane, int i) {
+    return (L * i + lane / kSpan) * (CW + 4) + lane % kSpan;
+  }
+};
+
+// The chunks whose outputs pass p (groups of outputs CW / 4 p ... of the
+// inverse) leaves in a wave's two tiles: pairs of 188 are n1 and 47 - n1.
+template <int F, int CW>
+constexpr int kMixPasses = (Mix<F>::NP + CW / 4 - 1) / (CW / 4);
+template <int F, int CW>
+constexpr int mix_chunk(int pass, int slot) {
+  return F == 188 ? (slot ? kMixChunks<F, CW> - 1 - pass : pass) : 2 * pass + slot;
+}
+template <int F, int CW>
+constexpr int mix_slots(int pass) {
+  const int c = mix_chunk<F, CW>(pass, 1);
+  return c >= kMixChunks<F, CW> || c == mix_chunk<F, CW>(pass, 0) ? 1 : 2;
+}
+
+// LDS accesses of a wave run in program order; this keeps the compiler to it
+// where lanes read what other lanes wrote
+__device__ __forceinline__ void wave_lds_fence() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// chunk CH of the lines from the tile to the lanes: a[n1] = x[4 n1 + n2]
+template <int F, int CW, int CH>
+__device__ __forceinline__ void mix_take(float2 (&a)[Mix<F>::Q], const float2* tile,
+                                         const MixLane& ln) {
+  constexpr int N = CW / 4;
+  wave_lds_fence();
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+    if (CH * N + k < Mix<F>::Q) {
+      a[CH * N + k] = tile[ln.line * (CW + 4) + 4 * k + ln.n2];
+      pin(a[CH * N + k]);
+    }
+  wave_lds_fence();
+}
+
+// the outputs of a pass to the two tiles
+template <int F, int CW, int PASS>
+__device__ __forceinline__ void mix_give(const float2 (&a)[Mix<F>::Q], float2* tiles,
+                                         const MixLane& ln) {
+  using C = Mix<F>;
+  constexpr int N = CW / 4;
+  wave_lds_fence();
+  static_for<N * PASS, (N * PASS + N < C::NP ? N * PASS + N : C::NP)>([&](auto i) {
+    float2 z[2];
+    mix_inv_out<F, i>(a, z);
+    static_for<0, 2>([&](auto e) {
+      if constexpr (e == 0 || C::hasB(i)) {
+        constexpr int n = mix_n<F>(i, e), ch = n / N;
+        constexpr int slot = ch == mix_chunk<F, CW>(PASS, 0) ? 0 : 1;
+        static_assert(ch == mix_chunk<F, CW>(PASS, slot), "the pass holds this chunk");
+        tiles[slot * kMixTile<CW> + ln.line * (CW + 4) + 4 * (n % N) + ln.n2] = z[e];
+      }
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  });
+  wave_lds_fence();
+}
+
+// Slot (view * nblk + line block) of block b when every line block of a view
+// runs on one XCD: the dispatcher sends block b to XCD b % 8, so XCD x takes
+// the views v = x, x + 8, ... whole, one after the other; the cache lines that
+// neighbouring line blocks share (intensities, ragged ends of rows) are then
+// fetched into its L2 once.  Bijective on whole groups of 8 views; the remaining blocks keep
+// their index.
 __device__ __forceinline__ int xcd_view_slot(int b, int n, int nblk) {
   const int full = (n / (8 * nblk)) * (8 * nblk);
   if (b >= full) return b;
@@ -304,201 +468,363 @@ __device__ __forceinline__ int xcd_view_slot(int b, int n, int nblk) {
   return (8 * (i / nblk) + x) * nblk + i % nblk;
 }
 
-// (2) DFT along CB columns of every mode of one view, the mode sum, the
-// modulus scale and the inverse DFT along the columns, in place in the
-// spectrum buffer.  Thread (c, tl, m) with c fastest.  All LDS is dynamic,
-// so the line buffers start at offset 0 and their 16-byte accesses are
-// aligned: CB * M line buffers, the mode powers s [M][CB][F], the scale g
-// [CB][F], then the twiddle tables (F + Q complex).
+// (1) Z = 2 P O - psi and the DFT along rows: one wave per 16 rows of a frame,
+// a quarter of a chunk's psi, P and O in flight while the one before is used
+// (more needs registers that cost a wave per SIMD).
+// grid (views x LB, modes)
 template <int F>
-__global__ __launch_bounds__(1024) void k_mix_cols(const ScanDev* __restrict__ scans,
-                                                   const int2* __restrict__ vmap,
-                                                   const float2* __restrict__ tw, int M, int CB,
-                                                   int direct) {
+__global__ __launch_bounds__(64, 4) void k_mix_rows_fwd(const ScanDev* __restrict__ scans,
+                                                        const int2* __restrict__ vmap,
+                                                        const float2* __restrict__ tw, int M) {
   using C = Mix<F>;
-  constexpr int R = C::R, Q = C::Q, QT = C::QT, H = C::H, LS = C::LS, FF = F * F;
-  extern __shared__ __align__(16) float2 dyn[];
-  const int t = threadIdx.x;
-  const int nblk = (F + CB - 1) / CB;
-  const int slot = xcd_view_slot(blockIdx.x, gridDim.x, nblk);
-  const int2 vm = vmap[slot / nblk];
+  constexpr int Q = C::Q, FF = F * F, CW = kRowCW, NCH = kMixChunks<F, CW>;
+  __shared__ float2 twl[4 * Q];
+  __shared__ float2 tile[kMixTile<CW>];
+  mix_load_twiddles<F>(tw, twl, threadIdx.x, 64);
+  const int lane = threadIdx.x;
+  const MixLane ln(lane);
+  const int slot = xcd_view_slot(blockIdx.x, gridDim.x, C::LB);
+  const int2 vm = vmap[slot / C::LB];
+  const ScanDev& sc = scans[vm.x];
+  const int j = uni(vm.y), m = blockIdx.y;
+  const int line0 = (slot % C::LB) * 16;
+  const int W = uni(sc.W);
+  const int y0 = uni(kidx(sc.pos)[2 * j]), x0 = uni(kidx(sc.pos)[2 * j + 1]);
+  const size_t frame = ((size_t)j * M + m) * FF;
+  const rsrc_t rpsi = make_rsrc(sc.psi + frame, (uint32_t)(FF * 8));
+  const rsrc_t rP = make_rsrc(sc.P + (size_t)m * FF, (uint32_t)(FF * 8));
+  const rsrc_t rO = make_rsrc(sc.O, (uint32_t)((size_t)uni(sc.H) * W * 8));
+  const int sF = line0 * F * 8, sO = ((y0 + line0) * W + x0) * 8;
+  float2 a[Q];
+  constexpr int U = 4;
+  float2 s[2][U], p[2][U], o[2][U];
+  // batch bt: quarter bt % 4 of chunk bt / 4
+  auto load = [&](auto bt) {
+    using K = MixIO<F, CW, bt / 4>;
+    constexpr int i0 = (bt % 4) * U;
+    asm volatile("" ::: "memory");
+    const int vF = K::load_off(lane, F), vO = K::load_off(lane, W);
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      if (i0 + k < K::kI) {
+        s[bt & 1][k] = bload2_nt(rpsi, vF, K::s(i0 + k, line0, F, sF));
+        p[bt & 1][k] = bload2(rP, vF, K::s(i0 + k, line0, F, sF));
+        o[bt & 1][k] = bload2(rO, vO, K::s(i0 + k, line0, W, sO));
+      }
+    asm volatile("" ::: "memory");
+  };
+  load(std::integral_constant<int, 0>{});
+  static_for<0, 4 * NCH>([&](auto bt) {
+    using K = MixIO<F, CW, bt / 4>;
+    constexpr int i0 = (bt % 4) * U;
+    if constexpr (bt + 1 < 4 * NCH) load(std::integral_constant<int, bt + 1>{});
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      if (i0 + k < K::kI) {
+        const float2 phi = cmul(p[bt & 1][k], o[bt & 1][k]);
+        tile[K::tile(lane, i0 + k)] =
+            make_float2(2.f * phi.x - s[bt & 1][k].x, 2.f * phi.y - s[bt & 1][k].y);
+      }
+    if constexpr (bt % 4 == 3) mix_take<F, CW, bt / 4>(a, tile, ln);
+  });
+  const rsrc_t rT =
+      make_rsrc(sc.tspec + ((size_t)j * M + m) * C::FT, (uint32_t)(C::FT * 8));
+  const MixSpec<F> sp(ln, line0 + ln.line);
+  mix_fwd<F>(a, twl, ln, [&](auto i, float2 x0v, float2 x1v) {
+    const int v = sp.at(i, ln);
+    bstore2_nt(rT, x0v, v, 0);
+    bstore2_nt(rT, x1v, v, MixSpec<F>::kX1);
+  });
+}
+
+// (2) DFT along the columns of 16 lines kx of every mode of one view, the mode
+// sum, the modulus scale and the inverse DFT, in place in the spectrum buffer.
+// A wave takes the modes w, w + NW, ... (one mode a wave up to 8 modes, above
+// six waves): it transforms them one after the other, keeps the last one's
+// spectrum in registers and transforms the others again once the scale is
+// known.  With several waves the mode powers go through LDS: one slot of 2 NP x
+// 64 per wave, then the scale.  A wave's tiles share its slot where they do not
+// meet its powers, i.e. up to 8 modes; above they follow the scale (six waves,
+// because eight would not fit).  A single mode needs only the tiles.
+constexpr int kMixWaves = 8, kMixWavesMany = 6;
+constexpr int mix_cols_waves(int M) { return M <= kMixWaves ? M : kMixWavesMany; }
+template <int F>
+constexpr size_t mix_cols_lds(int M) {
+  const size_t slots = M == 1 ? 0 : (size_t)(mix_cols_waves(M) + 1) * 2 * Mix<F>::NP * 64 * 4;
+  return slots +
+         (M == 1 ? 1 : M > kMixWaves ? kMixWavesMany : 0) * 2 * kMixTile<kColCW> * sizeof(float2);
+}
+
+template <int F, bool ONE>
+__global__ __launch_bounds__(ONE ? 64 : 64 * kMixWaves, F == 200 && !ONE ? 3 : 2) void k_mix_cols(
+    const ScanDev* __restrict__ scans, const int2* __restrict__ vmap,
+    const float2* __restrict__ tw, int M, int direct) {
+  using C = Mix<F>;
+  constexpr int Q = C::Q, NP = C::NP, FF = F * F, NE = 2 * NP, CW = kColCW;
+  __shared__ float2 twl[4 * Q];
+  extern __shared__ __align__(16) float pw[];  // [wave][NE][64], then the scale [NE][64]
+  static_assert(2 * kMixTile<kColCW> * 8 <= NE * 64 * 4, "the tiles fit a wave's slot");
+  const int t = threadIdx.x, nt = blockDim.x;
+  mix_load_twiddles<F>(tw, twl, t, nt);
+  const MixLane ln(t & 63);
+  const int lane = t & 63, w = ONE ? 0 : uni(t >> 6), NW = ONE ? 1 : nt >> 6;
+  const int slot = xcd_view_slot(blockIdx.x, gridDim.x, C::LB);
+  const int2 vm = vmap[slot / C::LB];
   const ScanDev& sc = scans[vm.x];
   const int j = uni(vm.y);
-  const int col0 = (slot % nblk) * CB;
-  const int c = t % CB;
-  const int rest = t / CB;
-  const int tl = rest % QT;
-  const int m = rest / QT;
-  const bool active = m < M && col0 + c < F;
-  const int line_id = m * CB + c;
-  float2* line = dyn + (size_t)line_id * LS;
-  float* s = reinterpret_cast<float*>(dyn + (size_t)CB * M * LS);
-  float* g = s + (size_t)M * CB * F;
-  float2* twl = reinterpret_cast<float2*>(g + (size_t)CB * F);  // F even: 8-byte aligned
-  float2* twq = twl + F;
-  float2* __restrict__ Tm = sc.tspec + ((size_t)j * M + m) * FF + col0 + c;
-  mix_load_tables<F>(tw, twl, twq, t, blockDim.x);
-  float2 a[R] = {};
-  if (active && tl < Q) {
+  const int line0 = (slot % C::LB) * 16;
+  const int line = line0 + ln.line;
+  const rsrc_t rI = make_rsrc(sc.I + (size_t)j * FF, (uint32_t)(FF * 4));
+  const float beta = sc.beta, inv_ff = 1.0f / (float)FF;
+  // g = sqrt(I / S) / F^2 (0 where S vanishes), or beta g - 1/F^2 for the
+  // update without psi
+  auto scale = [&](float iv, float s) {
+    const float g = (s > FLT_MIN) ? sqrtf(fmaxf(iv, 0.f) / s) * inv_ff : 0.f;
+    return direct ? beta * g - inv_ff : g;
+  };
+  // frequency ky of entry e of a lane in place (h, b)
+  auto freq = [&](int e, int h, int b) {
+    const int i = e >> 1;
+    return (h ? C::kB(i) : i) + Q * (b + 2 * (e & 1));
+  };
+  const int sT = line0 * C::LDT * 8;
+  float2* const tiles = M <= kMixWaves
+                            ? reinterpret_cast<float2*>(pw + w * NE * 64)
+                            : reinterpret_cast<float2*>(pw + (NW + 1) * NE * 64) +
+                                  w * 2 * kMixTile<CW>;
+  float2 x[NE];
+  const int nm = (M - w + NW - 1) / NW;  // this wave's modes
+  for (int it = 0; it < 2 * nm - 1; ++it) {
+    const int m = w + NW * (it < nm ? it : it - nm);
+    const rsrc_t rT =
+        make_rsrc(sc.tspec + ((size_t)j * M + m) * C::FT, (uint32_t)(C::FT * 8));
+    float2 a[Q];
+    {
+      // three chunks of the lines in flight
+      constexpr int NCH = kMixChunks<F, CW>, D = 3;
+      float2 r[D][8];
+      auto load = [&](auto c) {
+        using K = MixIO<F, CW, c>;
+        asm volatile("" ::: "memory");
+        const int v = K::load_off(lane, C::LDT);
 #pragma unroll
-    for (int n1 = 0; n1 < R; ++n1) a[n1] = Tm[(size_t)(Q * n1 + tl) * F];
-  }
-  __syncthreads();
-  if (active && tl < Q) mix_first<F, -1>(a, line, twl, tl);
-  __syncthreads();
-  if (active) mix_uv<F>(line, tl);
-  __syncthreads();
-  float2 lo[H], hi[H];
-  int ilo, ihi;
-  mix_pair_pos<F>(tl, ilo, ihi);
-  if (active) {
-    mix_pairs<F, -1>(lo, hi, line, twq, tl);  // spectrum at rows ilo + k, ihi + k
-    float* sl = s + (size_t)line_id * F;
+        for (int i = 0; i < K::kI; ++i) r[c % D][i] = bload2(rT, v, K::s(i, line0, C::LDT, sT));
+        asm volatile("" ::: "memory");
+      };
+      static_for<0, D>(load);
+      static_for<0, NCH>([&](auto c) {
+        using K = MixIO<F, CW, c>;
 #pragma unroll
-    for (int k = 0; k < H; ++k) {
-      sl[ilo + k] = cabs2(lo[k]);
-      if (ihi >= 0) sl[ihi + k] = cabs2(hi[k]);
+        for (int i = 0; i < K::kI; ++i) tiles[K::tile(lane, i)] = r[c % D][i];
+        if constexpr (c + D < NCH) load(std::integral_constant<int, c + D>{});
+        mix_take<F, CW, c>(a, tiles, ln);
+      });
     }
-  }
-  __syncthreads();
-  // one thread per pixel of the block's columns: sum over modes, scale
-  // sqrt(I / S) / F^2 (0 where S vanishes), or beta times that less 1/F^2
-  // for the update without psi; pixels in column-major order
-  const float* __restrict__ Ij = sc.I + (size_t)j * FF + col0;
-  const float inv_ff = 1.0f / (float)FF;
-  const float beta = sc.beta;
-  for (int p = t; p < CB * F; p += blockDim.x) {
-    const int cc = p / F, kk = p - cc * F;
-    if (col0 + cc >= F) continue;
-    float sum = 0.f;
-    for (int mm = 0; mm < M; ++mm) sum += s[(size_t)(mm * CB + cc) * F + kk];
-    const float iv = fmaxf(Ij[(size_t)kk * F + cc], 0.f);
-    const float gg = (sum > FLT_MIN) ? sqrtf(iv / sum) * inv_ff : 0.f;
-    g[cc * F + kk] = direct ? beta * gg - inv_ff : gg;
-  }
-  __syncthreads();
-  if (active) {
-    const float* gl = g + c * F;
+    mix_fwd<F>(a, twl, ln, [&](auto i, float2 x0v, float2 x1v) {
+      x[2 * i] = x0v;
+      x[2 * i + 1] = x1v;
+    });
+    if constexpr (ONE) {
+      // the wave's own powers are the mode sum; batches of 8 intensities
+      constexpr int U = 8;
 #pragma unroll
-    for (int k = 0; k < H; ++k) {
-      lo[k] = cscale(lo[k], gl[ilo + k]);
-      if (ihi >= 0) hi[k] = cscale(hi[k], gl[ihi + k]);
+      for (int e0 = 0; e0 < NE; e0 += U) {
+        float iv[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+          if (e0 + k < NE)
+            iv[k] = bload1(rI, line < F ? (freq(e0 + k, ln.h, ln.b) * F + line) * 4 : kMixOob, 0);
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+          if (e0 + k < NE) x[e0 + k] = cscale(x[e0 + k], scale(iv[k], cabs2(x[e0 + k])));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      float* const gs = pw + NW * NE * 64;
+      if (it < nm) {
+        float* const mine = pw + w * NE * 64 + lane;
+        if (it == 0) {
+#pragma unroll
+          for (int e = 0; e < NE; ++e) mine[e * 64] = cabs2(x[e]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < NE; ++e) mine[e * 64] += cabs2(x[e]);
+        }
+        if (it + 1 < nm) continue;
+        __syncthreads();
+        // the block's threads share the scale's entries; an entry's place
+        // follows from its lane
+        for (int q = t; q < NE * 64; q += nt) {
+          const int e = q >> 6;  // uniform in a wave
+          const int ky = freq(e, ln.h, ln.b);
+          const float iv = bload1(rI, line < F ? (ky * F + line) * 4 : kMixOob, 0);
+          float s = 0.f;
+          for (int k = 0; k < NW; ++k) s += pw[k * NE * 64 + q];
+          gs[q] = scale(iv, s);
+        }
+        __syncthreads();
+      }
+#pragma unroll
+      for (int e = 0; e < NE; ++e) x[e] = cscale(x[e], gs[e * 64 + lane]);
     }
-    // the forward reads of this line ended before the barriers above
-    mix_put_pairs<F>(line, lo, hi, tl);
-  }
-  __syncthreads();
-  mix_inverse<F>(a, line, twl, twq, tl, active);
-  if (active && tl < Q) {
+    mix_inv_in<F>(x, a, twl, ln);
+    static_for<0, kMixPasses<F, CW>>([&](auto pass) {
+      mix_give<F, CW, pass>(a, tiles, ln);
+      static_for<0, mix_slots<F, CW>(pass)>([&](auto slot) {
+        using K = MixIO<F, CW, mix_chunk<F, CW>(pass, slot)>;
 #pragma unroll
-    for (int n1 = 0; n1 < R; ++n1) Tm[(size_t)(Q * n1 + tl) * F] = a[n1];
+        for (int i = 0; i < K::kI; ++i)
+          bstore2(rT, tiles[slot * kMixTile<CW> + K::tile(lane, i)],
+                  K::store_off(lane, C::LDT, line0, i), K::s(i, line0, C::LDT, sT));
+      });
+    });
   }
 }
 
-// (3) inverse DFT along rows, psi' = psi + beta (Z' - P O), the view's
-// object numerator sum_m conj(P_m) psi'_m and the eps_psi partial sums; all
-// modes of RB rows per block.  The line buffers alternate between modes, so
-// a mode's spectrum rows go from global memory straight into the buffer the
-// previous mode did not use (its last readers passed the barriers of that
-// mode).  DIRECT: the column kernel scaled the spectra by beta g - 1/F^2, the
-// inverse is beta Z' - Z, and psi' = (2 - beta) P O + that (Eq. 3 with
-// psi = 2 P O - Z): psi is not read and the eps_psi partials are zero.
-template <int F, bool DIRECT>
-__device__ __forceinline__ void mix_rows_inv(const ScanDev* __restrict__ scans,
-                                             const int2* __restrict__ vmap,
-                                             const float2* __restrict__ tw, int M) {
+// (3) inverse DFT along rows, psi' = psi + beta (Z' - P O), the view's object
+// numerator sum_m conj(P_m) psi'_m and the eps_psi partial sums for 16 rows of
+// a view.  A wave takes the modes w, w + NW, ... (NW = min(M, kMixWaves) waves);
+// the outputs of its transform go to two tiles, two chunks of columns a pass,
+// where the update finds them row by row and leaves the mode's part of the
+// numerator in their place, to be added over the waves.  DIRECT: the
+// column kernel scaled the spectra by beta g - 1/F^2, the inverse is beta Z' -
+// Z, and psi' = (2 - beta) P O + that (Eq. 3 with psi = 2 P O - Z): psi is not
+// read and the eps_psi partials are zero.
+template <int F>
+constexpr size_t mix_inv_lds(int M) {
+  return (size_t)(M < kMixWaves ? M : kMixWaves) * 2 * kMixTile<kRowCW> * sizeof(float2);
+}
+
+template <int F, bool DIRECT, bool ONE>
+__global__ __launch_bounds__(ONE ? 64 : 64 * kMixWaves, 2) void k_mix_rows_inv(
+    const ScanDev* __restrict__ scans, const int2* __restrict__ vmap,
+    const float2* __restrict__ tw, int M) {
   using C = Mix<F>;
-  constexpr int R = C::R, Q = C::Q, QT = C::QT, RB = C::RB, LS = C::LS, NT = C::NT, FF = F * F;
-  __shared__ __align__(16) float2 xb[2 * RB * LS];
-  __shared__ float2 twl[F];
-  __shared__ float2 twq[Q];
-  __shared__ float red[2 * (NT / 64)];
-  const int t = threadIdx.x;
-  const int2 vm = vmap[blockIdx.x];
+  constexpr int Q = C::Q, NP = C::NP, FF = F * F, CW = kRowCW;
+  __shared__ float2 twl[4 * Q];
+  __shared__ float red[kMixWaves][2];
+  extern __shared__ float2 tiles[];  // [wave][2][tile]
+  const int t = threadIdx.x, nt = blockDim.x;
+  mix_load_twiddles<F>(tw, twl, t, nt);
+  const int lane = t & 63, w = ONE ? 0 : uni(t >> 6), NW = ONE ? 1 : nt >> 6;
+  const MixLane ln(lane);
+  float2* const mine = tiles + w * 2 * kMixTile<CW>;
+  const int bslot = xcd_view_slot(blockIdx.x, gridDim.x, C::LB);
+  const int2 vm = vmap[bslot / C::LB];
   const ScanDev& sc = scans[vm.x];
   const int j = uni(vm.y);
-  const int rl = t / QT, tl = t % QT;
-  const int row = blockIdx.y * RB + rl;
-  const bool active = rl < RB && row < F;
-  const bool owner = active && tl < Q;  // holds pixels Q n1 + tl of the row
+  const int lb = bslot % C::LB, line0 = lb * 16;
   const int W = uni(sc.W);
   const float beta = sc.beta;
   const int y0 = uni(kidx(sc.pos)[2 * j]), x0 = uni(kidx(sc.pos)[2 * j + 1]);
-  const float2* __restrict__ Or = sc.O + (size_t)(y0 + row) * W + x0;
-  mix_load_tables<F>(tw, twl, twq, t, NT);
-  float2 oacc[R];
-#pragma unroll
-  for (int n1 = 0; n1 < R; ++n1) oacc[n1] = make_float2(0.f, 0.f);
+  const MixSpec<F> sp(ln, line0 + ln.line);
+  const int sF = line0 * F * 8;
+  const rsrc_t rO = make_rsrc(sc.O, (uint32_t)((size_t)uni(sc.H) * W * 8));
+  const int sO = ((y0 + line0) * W + x0) * 8;
+  const rsrc_t ropart = make_rsrc(sc.opart + (size_t)j * FF, (uint32_t)(FF * 8));
   float e_d = 0.f, e_n = 0.f;
-  for (int m = 0; m < M; ++m) {
-    const size_t base = ((size_t)j * M + m) * FF + (size_t)row * F;
-    float2* line = xb + (m & 1) * (RB * LS) + rl * LS;
-    if (owner) {
-      const float4* __restrict__ Tr = reinterpret_cast<const float4*>(sc.tspec + base + R * tl);
-      float4* d = reinterpret_cast<float4*>(line + R * tl);
-#pragma unroll
-      for (int h = 0; h < R / 2; ++h) d[h] = Tr[h];
+  for (int m0 = 0; m0 < M; m0 += NW) {
+    // keeps what one round reads (the twiddles) out of the registers of the next
+    asm volatile("" ::: "memory");
+    const int m = m0 + w;
+    const bool on = ONE || m < M;  // uniform in a wave
+    const size_t frame = ((size_t)j * M + (on ? m : 0)) * FF;
+    const rsrc_t rT = make_rsrc(sc.tspec + ((size_t)j * M + (on ? m : 0)) * C::FT,
+                                (uint32_t)(C::FT * 8));
+    const rsrc_t rpsi = make_rsrc(sc.psi + frame, (uint32_t)(FF * 8));
+    const rsrc_t rP = make_rsrc(sc.P + (size_t)(on ? m : 0) * FF, (uint32_t)(FF * 8));
+    float2 a[Q];
+    if (on) {
+      float2 x[2 * NP];
+      static_for<0, NP>([&](auto i) {
+        const int v = sp.at(i, ln);
+        x[2 * i] = bload2_nt(rT, v, 0);
+        x[2 * i + 1] = bload2_nt(rT, v, MixSpec<F>::kX1);
+      });
+      mix_inv_in<F>(x, a, twl, ln);
     }
-    // the update's operands go out before the transform
-    float2* __restrict__ pm = sc.psi + base;
-    float2 pr[R], ov[R], pv[R];
-    if (owner) {
-      const float2* __restrict__ Pm = sc.P + (size_t)m * FF + (size_t)row * F;
+    static_for<0, kMixPasses<F, CW>>([&](auto pass) {
+      constexpr int kSlots = mix_slots<F, CW>(pass);
+      if (on) {
+        // the update of the pass's chunks, four indices a batch: the first
+        // batch's operands are in flight over the outputs, then the next one's
+        constexpr int U = 4, NB = kSlots * 4;
+        float2 p[2][U], o[2][U], s[2][U];
+        auto load = [&](auto bt) {
+          using K = MixIO<F, CW, mix_chunk<F, CW>(pass, bt / 4)>;
+          constexpr int i0 = (bt % 4) * U;
+          asm volatile("" ::: "memory");
+          const int vF = K::load_off(lane, F), vO = K::load_off(lane, W);
 #pragma unroll
-      for (int n1 = 0; n1 < R; ++n1) {
-        const int v = Q * n1 + tl;
-        pr[n1] = Pm[v];
-        ov[n1] = Or[v];
-        if constexpr (!DIRECT) pv[n1] = pm[v];
+          for (int k = 0; k < U; ++k)
+            if (i0 + k < K::kI) {
+              p[bt & 1][k] = bload2(rP, vF, K::s(i0 + k, line0, F, sF));
+              o[bt & 1][k] = bload2(rO, vO, K::s(i0 + k, line0, W, sO));
+              if constexpr (!DIRECT) s[bt & 1][k] = bload2_nt(rpsi, vF, K::s(i0 + k, line0, F, sF));
+            }
+          asm volatile("" ::: "memory");
+        };
+        load(std::integral_constant<int, 0>{});
+        mix_give<F, CW, pass>(a, mine, ln);
+        static_for<0, NB>([&](auto bt) {
+          using K = MixIO<F, CW, mix_chunk<F, CW>(pass, bt / 4)>;
+          constexpr int i0 = (bt % 4) * U;
+          if constexpr (bt + 1 < NB) load(std::integral_constant<int, bt + 1>{});
+#pragma unroll
+          for (int k = 0; k < U; ++k)
+            if (i0 + k < K::kI) {
+              const int v = K::store_off(lane, F, line0, i0 + k);
+              const int sr = K::s(i0 + k, line0, F, sF);
+              const bool in = K::in(lane, line0, i0 + k);
+              float2* const cell = mine + (bt / 4) * kMixTile<CW> + K::tile(lane, i0 + k);
+              const float2 z = *cell, pp = p[bt & 1][k];
+              const float2 phi = cmul(pp, o[bt & 1][k]);
+              float2 pn;
+              if constexpr (DIRECT) {
+                pn = make_float2((2.f - beta) * phi.x + z.x, (2.f - beta) * phi.y + z.y);
+              } else {
+                const float2 d = make_float2(beta * (z.x - phi.x), beta * (z.y - phi.y));
+                pn = cadd(s[bt & 1][k], d);
+                e_d += in ? cabs2(d) : 0.f;
+              }
+              e_n += in ? cabs2(pn) : 0.f;
+              bstore2_nt(rpsi, pn, v, sr);
+              const float2 q = cmulc(pp, pn);
+              if constexpr (ONE) bstore2(ropart, q, v, sr);
+              else *cell = q;
+            }
+        });
       }
-    }
-    __syncthreads();  // the rows (and, in the first mode, the tables)
-    float2 a[R] = {};
-    mix_inverse<F>(a, line, twl, twq, tl, active);  // a[n1] = Z' at column Q n1 + tl
-    if (owner) {
-#pragma unroll
-      for (int n1 = 0; n1 < R; ++n1) {
-        const float2 phi = cmul(pr[n1], ov[n1]);
-        float2 pn;
-        if constexpr (DIRECT) {
-          pn = make_float2((2.f - beta) * phi.x + a[n1].x, (2.f - beta) * phi.y + a[n1].y);
-        } else {
-          const float2 d = make_float2(beta * (a[n1].x - phi.x), beta * (a[n1].y - phi.y));
-          pn = cadd(pv[n1], d);
-          e_d += cabs2(d);
-        }
-        pm[Q * n1 + tl] = pn;
-        e_n += cabs2(pn);
-        oacc[n1] = cadd(oacc[n1], cmulc(pr[n1], pn));
+      if constexpr (!ONE) {
+        const int nw = min(NW, M - m0);
+        __syncthreads();
+        static_for<0, kSlots>([&](auto slot) {
+          using K = MixIO<F, CW, mix_chunk<F, CW>(pass, slot)>;
+          for (int i = w; i < K::kI; i += NW) {
+            const int v = K::store_off(lane, F, line0, i), so = K::s(i, line0, F, sF);
+            float2 q = m0 ? bload2(ropart, v, so) : make_float2(0.f, 0.f);
+            for (int k = 0; k < nw; ++k)
+              q = cadd(q, tiles[(k * 2 + slot) * kMixTile<CW> + K::tile(lane, i)]);
+            bstore2(ropart, q, v, so);
+          }
+        });
+        __syncthreads();
       }
-    }
+    });
   }
-  if (owner) {
-    float2* __restrict__ oj = sc.opart + (size_t)j * FF + (size_t)row * F;
-#pragma unroll
-    for (int n1 = 0; n1 < R; ++n1) oj[Q * n1 + tl] = oacc[n1];
+  e_d = wave_sum(e_d);
+  e_n = wave_sum(e_n);
+  if constexpr (!ONE) {
+    if (lane == 0) { red[w][0] = e_d; red[w][1] = e_n; }
+    __syncthreads();
+    e_d = e_n = 0.f;
+    for (int k = 0; k < NW; ++k) { e_d += red[k][0]; e_n += red[k][1]; }
   }
-  block_sum2<NT>(e_d, e_n, red);
   if (t == 0) {
-    const int part = j * gridDim.y + blockIdx.y;
+    const int part = j * C::LB + lb;
     sc.err_psi[2 * part] = e_d;
     sc.err_psi[2 * part + 1] = e_n;
   }
-}
-
-template <int F>
-__global__ __launch_bounds__(Mix<F>::NT) void k_mix_rows_inv(const ScanDev* __restrict__ scans,
-                                                             const int2* __restrict__ vmap,
-                                                             const float2* __restrict__ tw,
-                                                             int M) {
-  mix_rows_inv<F, false>(scans, vmap, tw, M);
-}
-
-template <int F>
-__global__ __launch_bounds__(Mix<F>::NT) void k_mix_rows_inv_direct(
-    const ScanDev* __restrict__ scans, const int2* __restrict__ vmap,
-    const float2* __restrict__ tw, int M) {
-  mix_rows_inv<F, true>(scans, vmap, tw, M);
 }
 
 }  // namespace dmk

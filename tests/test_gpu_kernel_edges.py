@@ -28,3 +28,14 @@ def test_probe_division_over_chunks_and_modes(seed, n, f, m):
 def test_bf16x3_mode_counts(seed, n, m):
     say(f"case bf16x3 modes seed={seed} N={n} M={m}")
     bf16x3.compare(synth.random_case(seed, n, 128, m, 190, 200, perturb=0.3))
+
+
+# the mixed-radix frames: modes shared out over the waves of a block (up to 8
+# one each; above, the column kernel takes six waves, the inverse row kernel
+# eight, with the last round part empty), the single-mode forms, and view
+# counts with whole groups of eight views per XCD map and a remainder
+@pytest.mark.parametrize("seed,n,f,m", [(101, 8, 188, 1), (102, 17, 200, 1), (103, 16, 188, 2),
+                                        (104, 9, 200, 7), (105, 5, 188, 9), (106, 5, 200, 13)])
+def test_mixed_radix_modes_and_views(seed, n, f, m):
+    say(f"case mixed radix modes seed={seed} N={n} F={f} M={m}")
+    one_step_case(synth.random_case(seed, n, f, m, f + 60, f + 55, perturb=0.5))
