@@ -18,6 +18,7 @@
 #include "dm_kernels.hpp"
 #include "dm_mfma.hpp"
 #include "dm_mixed.hpp"
+#include "dm_mixed_few.hpp"
 #include "dm_order.hpp"
 #include "dm_modes.hpp"
 #include "dm_ortho.hpp"
@@ -130,10 +131,47 @@ size_t spectrum_frame(int F) {
 // row blocks per frame of the three-kernel path (one eps_psi partial each)
 int row_parts(int F) {
   switch (F) {
-    case 188: return dmk::Mix<188>::LB;
-    case 200: return dmk::Mix<200>::LB;
+    case 188: return dmk::Few<188>::NBLK;  // more than dm_mixed.hpp's line blocks
+    case 200: return dmk::Few<200>::NBLK;
   }
   return F / row_block(F);
+}
+
+// Whether a batch of frames of 188 or 200 pixels (views x modes) takes the
+// kernels of dm_mixed_few.hpp: start of the unrolled ones costs more than they
+// gain below these counts (two iterations with checkpoint, here against there:
+// 188^2 x 1 mode 145 / 194 us at 12 frames, 281 / 287 at 84, 405 / 406 at 150;
+// x 4 511 / 522 at 240; x 2 3113 / 2798 at 1600; 200^2 251 / 259 at 60 and 296 /
+// 282 at 90 frames).
+bool is_few(int F, int views, int M) {
+  return (long)views * M < (F == 188 ? 512 : 80);
+}
+
+// threads per line of the few-frame mixed-radix transforms (Q + 1)
+int few_qt(int F) { return F == 188 ? dmk::Few<188>::QT : dmk::Few<200>::QT; }
+
+// columns per block of the few-frame mixed-radix column kernel: a power of two up to
+// 16 with CB * M * (Q + 1) threads (rounded to whole waves) at most 512.
+// The kernel is bound by its arithmetic and barriers, and smaller blocks
+// overlap one block's barriers with another's work: at 10000 x 4 x 188^2
+// blocks of 384 threads (CB = 2) take 12.6 ms against 15.0 ms with 768
+// (CB = 4); with 192 (CB = 1) the view update is 1.3 ms slower again.
+int few_cols_per_block(int F, int M) {
+  const int QT = few_qt(F);
+  int p = 1;
+  while (p * 2 <= 16 && ((p * 2 * M * QT + 63) / 64) * 64 <= 512) p *= 2;
+  return p;
+}
+
+int few_cols_threads(int F, int M, int cb) { return ((cb * M * few_qt(F) + 63) / 64) * 64; }
+
+// dynamic LDS of the few-frame mixed-radix column kernel: cb * M exchange lines of
+// Q * R + 2 complex values, the mode powers [M][cb][F], the scale [cb][F]
+// and the twiddle tables (F + Q complex)
+size_t few_cols_lds_bytes(int F, int M, int cb) {
+  const int Q = few_qt(F) - 1;
+  return (size_t)cb * M * (F + 2) * sizeof(float2) + (size_t)(M + 1) * cb * F * sizeof(float) +
+         (size_t)(F + Q) * sizeof(float2);
 }
 
 // ---------------------------------------------------------------------------
@@ -511,6 +549,12 @@ hipError_t set_mixed_lds(int M) {
   return e;
 }
 
+// eps_psi partials per view that the mixed-radix kernels of a batch write
+int mixed_parts(int F, int views, int M) {
+  if (is_few(F, views, M)) return row_parts(F);
+  return F == 188 ? dmk::Mix<188>::LB : dmk::Mix<200>::LB;
+}
+
 // (Re)build everything that depends on the tuning: tile lists, chunking, the
 // scan descriptor table and the block maps; upload them.  Synchronises.
 dm_status apply_tuning(dm_ctx* c, const dm_tuning& t) {
@@ -569,6 +613,7 @@ dm_status apply_tuning(dm_ctx* c, const dm_tuning& t) {
     v.C = S.C;
     v.chunk = S.chunk;
     v.n_psi_parts = is_bf16x3(S.d)  ? 2 * S.d.n_frames
+                    : is_mixed(c->F) ? S.d.n_frames * mixed_parts(c->F, c->total_views, c->M)
                     : t.view_path == DM_VIEWS_THREE_KERNEL ? L.n_psi_parts_multi
                                     : L.n_psi_parts_fused;
     v.beta = S.d.beta;
@@ -585,7 +630,14 @@ dm_status apply_tuning(dm_ctx* c, const dm_tuning& t) {
   DM_HIP(c, hipMemcpyAsync(c->cmap(), cmap.data(), cmap.size() * sizeof(int2),
                            hipMemcpyHostToDevice, c->stream));
   if (t.view_path == DM_VIEWS_THREE_KERNEL && is_mixed(c->F)) {
-    DM_HIP(c, c->F == 188 ? set_mixed_lds<188>(c->M) : set_mixed_lds<200>(c->M));
+    if (is_few(c->F, c->total_views, c->M)) {
+      const int lds = (int)few_cols_lds_bytes(c->F, c->M, few_cols_per_block(c->F, c->M));
+      const void* k = c->F == 188 ? reinterpret_cast<const void*>(dmk::k_few_cols<188>)
+                                  : reinterpret_cast<const void*>(dmk::k_few_cols<200>);
+      DM_HIP(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    } else {
+      DM_HIP(c, c->F == 188 ? set_mixed_lds<188>(c->M) : set_mixed_lds<200>(c->M));
+    }
   } else if (t.view_path == DM_VIEWS_THREE_KERNEL) {
     const int MT = c->M * c->L;
     const int lds = (int)cols_lds_bytes(c->F, MT, cols_per_block(c->F, MT));
@@ -690,8 +742,33 @@ dm_status launch_views_mixed_modes(dm_ctx* c, bool direct) {
   return DM_OK;
 }
 
+// Frames of edge F = R * Q (188, 200), few of them: the same three passes with
+// the lines in LDS.
+template <int F>
+dm_status launch_views_few(dm_ctx* c, bool direct) {
+  using C = dmk::Few<F>;
+  const int M = c->M;
+  hipLaunchKernelGGL(dmk::k_few_rows_fwd<F>, dim3(c->total_views, C::NBLK), dim3(C::NT), 0,
+                     c->stream, c->scan_dev(), c->vmap(), c->tw(), M);
+  DM_LAUNCHED(c, "k_few_rows_fwd");
+  const int cb = few_cols_per_block(F, M);
+  hipLaunchKernelGGL(dmk::k_few_cols<F>, dim3(c->total_views * ((F + cb - 1) / cb)),
+                     dim3(few_cols_threads(F, M, cb)), few_cols_lds_bytes(F, M, cb), c->stream,
+                     c->scan_dev(), c->vmap(), c->tw(), M, cb, direct ? 1 : 0);
+  DM_LAUNCHED(c, "k_few_cols");
+  if (direct)
+    hipLaunchKernelGGL(dmk::k_few_rows_inv_direct<F>, dim3(c->total_views, C::NBLK),
+                       dim3(C::NT), 0, c->stream, c->scan_dev(), c->vmap(), c->tw(), M);
+  else
+    hipLaunchKernelGGL(dmk::k_few_rows_inv<F>, dim3(c->total_views, C::NBLK), dim3(C::NT), 0,
+                       c->stream, c->scan_dev(), c->vmap(), c->tw(), M);
+  DM_LAUNCHED(c, "k_few_rows_inv");
+  return DM_OK;
+}
+
 template <int F>
 dm_status launch_views_mixed(dm_ctx* c, bool direct) {
+  if (is_few(F, c->total_views, c->M)) return launch_views_few<F>(c, direct);
   return c->M == 1 ? launch_views_mixed_modes<F, true>(c, direct)
                    : launch_views_mixed_modes<F, false>(c, direct);
 }

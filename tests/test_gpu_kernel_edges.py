@@ -30,12 +30,15 @@ def test_bf16x3_mode_counts(seed, n, m):
     bf16x3.compare(synth.random_case(seed, n, 128, m, 190, 200, perturb=0.3))
 
 
-# the mixed-radix frames: modes shared out over the waves of a block (up to 8
-# one each; above, the column kernel takes six waves, the inverse row kernel
-# eight, with the last round part empty), the single-mode forms, and view
-# counts with whole groups of eight views per XCD map and a remainder
-@pytest.mark.parametrize("seed,n,f,m", [(101, 8, 188, 1), (102, 17, 200, 1), (103, 16, 188, 2),
-                                        (104, 9, 200, 7), (105, 5, 188, 9), (106, 5, 200, 13)])
+# the mixed-radix frames from the frame counts on where the unrolled kernels
+# run (512 at 188^2, 80 at 200^2; the last two just below): modes shared out
+# over the waves of a block (up to 8 one each; above, the column kernel takes
+# six waves, the inverse row kernel eight, with the last round part empty), the
+# single-mode forms, and view counts with whole groups of eight views per XCD
+# map and a remainder
+@pytest.mark.parametrize("seed,n,f,m", [(101, 513, 188, 1), (102, 80, 200, 1), (103, 256, 188, 2),
+                                        (104, 13, 200, 7), (105, 57, 188, 9), (106, 8, 200, 13),
+                                        (107, 511, 188, 1), (108, 39, 200, 2)])
 def test_mixed_radix_modes_and_views(seed, n, f, m):
     say(f"case mixed radix modes seed={seed} N={n} F={f} M={m}")
     one_step_case(synth.random_case(seed, n, f, m, f + 60, f + 55, perturb=0.5))
