@@ -157,6 +157,12 @@ int vgrad_chunks(const dmnet_desc& d, const Conv& c, int n) {
   return (int)((n * hw + kVGradChunk - 1) / kVGradChunk);
 }
 
+// blocks of k_grad_prep (one bias partial per channel each)
+int prep_blocks(const dmnet_desc& d, const Conv& c, int n) {
+  const long hw = (long)(d.size >> c.level) * (d.size >> c.level);
+  return (int)((n * hw + dmn::kPrepPix - 1) / dmn::kPrepPix);
+}
+
 constexpr int kMseBlocks = 256;
 
 NetLayout net_layout(const dmnet_desc& d, const Shape& s, const ActLayout& a) {
@@ -209,6 +215,7 @@ NetLayout net_layout(const dmnet_desc& d, const Shape& s, const ActLayout& a) {
       wpart = std::max(wpart, (size_t)wgrad_chunks(d, c, d.batch) * c.cout * c.cin * 9);
     wpart = std::max(wpart, (size_t)vgrad_chunks(d, c, d.batch) * c.cout *
                                 (1 + (size_t)c.cin * c.k * c.k));
+    wpart = std::max(wpart, (size_t)prep_blocks(d, c, d.batch) * c.cout);
   }
   L.wpart = take(wpart * 4);
   L.partial = take(kMseBlocks * 4);
@@ -451,7 +458,7 @@ dm_status conv_bwd(dmnet* net, const Conv& c, const float* x, long x_ns, const f
       // bfloat16 copies: x shifted by each column offset, and dz
       uint16_t* xs3 = net->wgb();
       uint16_t* dzb = xs3 + (size_t)3 * n * c.cin * H * W;
-      hipLaunchKernelGGL(dmn::k_to_bf16_shift3, dim3(grid_for((long)n * c.cin * H * W)),
+      hipLaunchKernelGGL(dmn::k_to_bf16_shift3, dim3(grid_for((long)n * c.cin * H * W / 8)),
                          dim3(256), 0, net->stream, x, c.cin, H, W, x_ns, n, xs3);
       NET_LAUNCHED(net, "k_to_bf16_shift3");
       hipLaunchKernelGGL(dmn::k_to_bf16_nchw, dim3(grid_for((long)n * c.cout * H * W)),
@@ -555,6 +562,52 @@ dm_status relu_mask(dmnet* net, float* g, const float* act, long ns, long per, i
   hipLaunchKernelGGL(dmn::k_relu_mask, dim3(grid_for(per * n)), dim3(256), 0, net->stream, g, ns,
                      act, ns, per, n);
   NET_LAUNCHED(net, "k_relu_mask");
+  return DM_OK;
+}
+
+// Backward through ReLU and the 3x3 convolution c before it: g is the gradient
+// of the activation act (both with sample stride ns), to which the pooling
+// gradient gp of the pooled activation is added first where given; then as
+// conv_bwd.  On the chunk path with rows of a multiple of 8 one kernel prepares
+// the gradient in all the forms its consumers read.
+dm_status relu_conv_bwd(dmnet* net, const Conv& c, const float* x, long x_ns, float* g,
+                        const float* act, const float* gp, long ns, float* dx, int S, int n) {
+  if (!net->chunked() || S % 8) {
+    if (gp) {
+      const long per = (long)c.cout * S * S;
+      hipLaunchKernelGGL(dmn::k_avgpool2_bwd_add, dim3(grid_for(per * n)), dim3(256), 0,
+                         net->stream, gp, ns, g, ns, c.cout, S, S, n);
+      NET_LAUNCHED(net, "k_avgpool2_bwd_add");
+    }
+    NET_TRY(relu_mask(net, g, act, ns, (long)c.cout * S * S, n));
+    return conv_bwd(net, c, x, x_ns, g, ns, dx, ns, S, S, n);
+  }
+  const long np = (long)n * S * S;
+  uint16_t* xs3 = net->wgb();
+  uint16_t* dzb = xs3 + (size_t)3 * c.cin * np;
+  float* part = net->f(net->L.wpart);
+  const int blocks = prep_blocks(net->d, c, n);
+  hipLaunchKernelGGL(dmn::k_grad_prep, dim3(blocks, c.cout / 32), dim3(256), 0, net->stream, g,
+                     ns, act, ns, gp, ns, c.cout, S, S, n, net->xcl(), dzb, part);
+  NET_LAUNCHED(net, "k_grad_prep");
+  hipLaunchKernelGGL(dmn::k_bias_sum, dim3(c.cout), dim3(256), 0, net->stream, part, blocks,
+                     c.cout, net->grads() + c.b_off);
+  NET_LAUNCHED(net, "k_bias_sum");
+  hipLaunchKernelGGL(dmn::k_to_bf16_shift3, dim3(grid_for(np * c.cin / 8)), dim3(256), 0,
+                     net->stream, x, c.cin, S, S, x_ns, n, xs3);
+  NET_LAUNCHED(net, "k_to_bf16_shift3");
+  const int K = c.cin * 9, nch = wgrad_chunks(net->d, c, n);
+  hipLaunchKernelGGL(dmn::k_conv3_wgrad_mfma_s, dim3((K + 255) / 256, (c.cout + 31) / 32, nch),
+                     dim3(256), 0, net->stream, xs3, c.cin, S, S, dzb, c.cout, n, kWgradChunk,
+                     part);
+  NET_LAUNCHED(net, "k_conv3_wgrad_mfma_s");
+  const long cnt = (long)c.cout * K;
+  hipLaunchKernelGGL(dmn::k_sum_chunks, dim3(grid_for(cnt)), dim3(256), 0, net->stream, part, nch,
+                     cnt, net->grads() + c.w_off);
+  NET_LAUNCHED(net, "k_sum_chunks");
+  if (dx)
+    NET_TRY(conv3(net, {{net->xcl(), c.cout / 32, 0}, {nullptr, 0, 0}, S, S, n,
+                        net->wpt() + c.w_off, nullptr, nullptr, dx, c.cin, ns, false}));
   return DM_OK;
 }
 
@@ -683,13 +736,10 @@ dm_status backward(dmnet* net, const float* x, int n, float* dy) {
   // decoder, l = 0 .. L-2 (reverse of the forward order)
   for (int l = 0; l <= L - 2; ++l) {
     const int S = d.size >> l;
-    const long per = (long)s.ch[l] * S * S;
-    NET_TRY(relu_mask(net, net->gact(a.dec_out[l]), net->act(a.dec_out[l]), T, per, n));
-    NET_TRY(conv_bwd(net, s.convs[ci--], net->act(a.dec_mid[l]), T, net->gact(a.dec_out[l]), T,
-                     net->gact(a.dec_mid[l]), T, S, S, n));
-    NET_TRY(relu_mask(net, net->gact(a.dec_mid[l]), net->act(a.dec_mid[l]), T, per, n));
-    NET_TRY(conv_bwd(net, s.convs[ci--], net->act(a.cat[l]), T, net->gact(a.dec_mid[l]), T,
-                     net->gact(a.cat[l]), T, S, S, n));
+    NET_TRY(relu_conv_bwd(net, s.convs[ci--], net->act(a.dec_mid[l]), T, net->gact(a.dec_out[l]),
+                          net->act(a.dec_out[l]), nullptr, T, net->gact(a.dec_mid[l]), S, n));
+    NET_TRY(relu_conv_bwd(net, s.convs[ci--], net->act(a.cat[l]), T, net->gact(a.dec_mid[l]),
+                          net->act(a.dec_mid[l]), nullptr, T, net->gact(a.cat[l]), S, n));
     // gradient of the upsampled part goes to the next-deeper output
     float* dh = (l + 1 <= L - 2) ? net->gact(a.dec_out[l + 1]) : net->gact(a.bott);
     const long tot = (long)s.ch[l + 1] * (S / 2) * (S / 2) * n;
@@ -700,22 +750,15 @@ dm_status backward(dmnet* net, const float* x, int n, float* dy) {
   // encoder, l = L-1 .. 0
   for (int l = L - 1; l >= 0; --l) {
     const int S = d.size >> l;
-    const long per = (long)s.ch[l] * S * S;
     float* g_out = net->gact(a.enc_out[l]);  // skip slice of the concat gradient, or bottleneck
-    if (l < L - 1) {
-      hipLaunchKernelGGL(dmn::k_avgpool2_bwd_add, dim3(grid_for(per * n)), dim3(256), 0,
-                         net->stream, net->gact(a.pool[l]), T, g_out, T, s.ch[l], S, S, n);
-      NET_LAUNCHED(net, "k_avgpool2_bwd_add");
-    }
-    NET_TRY(relu_mask(net, g_out, net->act(a.enc_out[l]), T, per, n));
-    NET_TRY(conv_bwd(net, s.convs[ci--], net->act(a.enc_mid[l]), T, g_out, T,
-                     net->gact(a.enc_mid[l]), T, S, S, n));
-    NET_TRY(relu_mask(net, net->gact(a.enc_mid[l]), net->act(a.enc_mid[l]), T, per, n));
+    NET_TRY(relu_conv_bwd(net, s.convs[ci--], net->act(a.enc_mid[l]), T, g_out,
+                          net->act(a.enc_out[l]), l < L - 1 ? net->gact(a.pool[l]) : nullptr, T,
+                          net->gact(a.enc_mid[l]), S, n));
     const float* in = (l == 0) ? x : net->act(a.pool[l - 1]);
     const long in_ns = (l == 0) ? (long)d.size * d.size : T;
     float* g_in = (l == 0) ? nullptr : net->gact(a.pool[l - 1]);
-    NET_TRY(conv_bwd(net, s.convs[ci--], in, in_ns, net->gact(a.enc_mid[l]), T, g_in, T, S, S,
-                     n));
+    NET_TRY(relu_conv_bwd(net, s.convs[ci--], in, in_ns, net->gact(a.enc_mid[l]),
+                          net->act(a.enc_mid[l]), nullptr, T, g_in, S, n));
   }
   return DM_OK;
 }

@@ -372,4 +372,82 @@ __global__ void k_to_chunk16(const float* __restrict__ x, int C, int HW, long x_
   }
 }
 
+// ---------------------------------------------------------------------------
+// What the backward pass of a 3x3 convolution needs of its output gradient g
+// (float32 [n][C][H][W], sample stride g_ns), in one pass over it: g plus,
+// where gp is given, the gradient of a 2x2 average pooling (0.25 gp of the
+// pooled pixel), zero where the activation is not positive, as
+//   dz16  chunk layout (data gradient), dzn  bfloat16 NCHW (weight gradient),
+//   dbp[block][c]  the block's float32 sums (bias gradient, unrounded).
+// The five kernels that did this (pooling gradient, mask, two conversions,
+// bias sums) read and wrote the gradient seven times.
+// Block: 32 channels x 64 pixels a step, kPrepPix pixels; C a multiple of 32, H*W
+// of 64, W of 8.  grid (ceil(n H W / kPrepPix), C / 32)
+// ---------------------------------------------------------------------------
+constexpr int kPrepPix = 256;
+__global__ __launch_bounds__(256) void k_grad_prep(const float* __restrict__ g, long g_ns,
+                                                   const float* __restrict__ act, long a_ns,
+                                                   const float* __restrict__ gp, long gp_ns,
+                                                   int C, int H, int W, int n,
+                                                   uint16_t* __restrict__ dz16,
+                                                   uint16_t* __restrict__ dzn,
+                                                   float* __restrict__ dbp) {
+  __shared__ uint16_t tile[64][32 + 8];  // [pixel][channel]
+  const int t = threadIdx.x, cl = t >> 3, c = blockIdx.y * 32 + cl;
+  const int HW = H * W, NP = n * HW;
+  float sum = 0.f;
+  for (int P0 = blockIdx.x * kPrepPix; P0 < min(NP, (int)(blockIdx.x + 1) * kPrepPix); P0 += 64) {
+    const int smp = P0 / HW, p = P0 - smp * HW + 8 * (t & 7);
+    const long off = (long)c * HW + p;
+    const float4* __restrict__ gs = reinterpret_cast<const float4*>(g + smp * g_ns + off);
+    const float4* __restrict__ as = reinterpret_cast<const float4*>(act + smp * a_ns + off);
+    const float4 g0 = gs[0], g1 = gs[1], a0 = as[0], a1 = as[1];
+    float v[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+    const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+    if (gp) {
+      const int i = p / W, j = p - i * W;
+      const float* __restrict__ q =
+          gp + smp * gp_ns + (long)c * (HW / 4) + (i / 2) * (W / 2) + j / 2;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] += 0.25f * q[k / 2];
+    }
+    uint16_t h[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (!(a[k] > 0.f)) v[k] = 0.f;
+      sum += v[k];
+      h[k] = f_to_bf16_bits(v[k]);
+    }
+    uint32_t u[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) u[k] = (uint32_t)h[2 * k] | ((uint32_t)h[2 * k + 1] << 16);
+    *reinterpret_cast<uint4*>(dzn + ((long)smp * C + c) * HW + p) =
+        make_uint4(u[0], u[1], u[2], u[3]);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) tile[8 * (t & 7) + k][cl] = h[k];
+    __syncthreads();
+    // 64 pixels x 32 channels are 4 KB of consecutive chunk layout
+    *reinterpret_cast<uint4*>(dz16 + ((size_t)blockIdx.y * NP + P0) * 32 + t * 8) =
+        *reinterpret_cast<const uint4*>(&tile[t >> 2][8 * (t & 3)]);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) sum += __shfl_xor(sum, o, 64);
+  if ((t & 7) == 0) dbp[(long)blockIdx.x * C + c] = sum;
+}
+
+// db[c] = sum over blocks of dbp[block][c]; one block of 256 threads per c
+__global__ __launch_bounds__(256) void k_bias_sum(const float* __restrict__ dbp, int blocks,
+                                                  int C, float* __restrict__ db) {
+  __shared__ float red[4];
+  const int c = blockIdx.x, t = threadIdx.x;
+  float s = 0.f;
+  for (int b = t; b < blocks; b += 256) s += dbp[(long)b * C + c];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if ((t & 63) == 0) red[t >> 6] = s;
+  __syncthreads();
+  if (t == 0) db[c] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
 }  // namespace dmn

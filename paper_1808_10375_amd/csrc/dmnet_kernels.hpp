@@ -350,22 +350,28 @@ __global__ __launch_bounds__(256) void k_conv3_mfma_cl(const uint16_t* __restric
 // the input shifted by each column offset of the 3 x 3 taps, so that 8
 // consecutive output pixels of a row read 8 consecutive, 16-byte aligned
 // values for every tap; x float32 [n][C][H*W], sample stride x_ns.
+// W a multiple of 8; eight pixels a thread: one read and three 16-byte stores
+// (a pixel a thread: 15.6 us on average over the convolutions of 32 samples of
+// 64 x 64 against 8.1).
 __global__ void k_to_bf16_shift3(const float* __restrict__ x, int C, int H, int W, long x_ns,
-                                 int n, uint16_t* __restrict__ xs3) {
-  const long per = (long)n * C * H * W;
-  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < per;
+                                    int n, uint16_t* __restrict__ xs3) {
+  const long HW = (long)H * W, per = (long)n * C * HW, total = per / 8;
+  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < total;
        e += (long)gridDim.x * blockDim.x) {
-    const int j = (int)(e % W);
-    const long r = e / W;  // (s * C + c) * H + i
-    const int i = (int)(r % H);
-    const long sc = r / H;
-    const int c = (int)(sc % C), smp = (int)(sc / C);
-    const float* __restrict__ row = x + (long)smp * x_ns + ((long)c * H + i) * W;
+    const long sc = e * 8 / HW;
+    const int r = (int)(e * 8 - sc * HW), j = r % W;
+    const int smp = (int)(sc / C), c = (int)(sc - (long)smp * C);
+    const float* __restrict__ s = x + (long)smp * x_ns + (long)c * HW + r;
+    uint32_t h[10];  // pixels j - 1 .. j + 8
+    h[0] = j > 0 ? f_to_bf16_bits(s[-1]) : 0;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const int jj = j + d - 1;
-      xs3[(long)d * per + e] = ((unsigned)jj < (unsigned)W) ? f_to_bf16_bits(row[jj]) : 0;
-    }
+    for (int k = 0; k < 8; ++k) h[k + 1] = f_to_bf16_bits(s[k]);
+    h[9] = j + 8 < W ? f_to_bf16_bits(s[8]) : 0;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+      *reinterpret_cast<uint4*>(xs3 + d * per + e * 8) =
+          make_uint4(h[d] | (h[d + 1] << 16), h[d + 2] | (h[d + 3] << 16),
+                     h[d + 4] | (h[d + 5] << 16), h[d + 6] | (h[d + 7] << 16));
   }
 }
 
