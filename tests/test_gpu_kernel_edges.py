@@ -1,6 +1,7 @@
 """One iteration against the FP64 oracle at the sizes where the smaller
 kernels of the iteration can go wrong (remainders of their batches, the last
 and the first size of a split)."""
+import numpy as np
 import pytest
 
 from paper_1808_10375_amd import synth
@@ -42,3 +43,26 @@ def test_bf16x3_mode_counts(seed, n, m):
 def test_mixed_radix_modes_and_views(seed, n, f, m):
     say(f"case mixed radix modes seed={seed} N={n} F={f} M={m}")
     one_step_case(synth.random_case(seed, n, f, m, f + 60, f + 55, perturb=0.5))
+
+
+# a checkpoint's views go in and out bit for bit: just below and above the size
+# from which a kernel streams them (64 MB; blocks of 4096 words of 16 bytes, the
+# last one partial), and from and to addresses 8 bytes off a 16-byte boundary
+@pytest.mark.parametrize("n,f,shift", [(63, 256, 0), (129, 256, 0), (238, 188, 0), (130, 256, 1)])
+def test_checkpoint_views_round_trip(n, f, shift):
+    import torch
+    from paper_1808_10375_amd import dm
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev)
+    g.manual_seed(n)
+    c = synth.random_case(111, n, f, 1, f + 9, f + 12)
+    ctx = dm.DMContext(torch.from_numpy(c["I"]).to(dev), c["pos"], torch.from_numpy(c["P"]).to(dev),
+                       torch.from_numpy(c["O"]).to(dev))
+    flat = torch.randn(2 * (n * f * f + shift), generator=g, device=dev)
+    psi = torch.view_as_complex(flat[2 * shift:].view(n, 1, f, f, 2))
+    ctx.set_state(psi, torch.from_numpy(c["P"]).to(dev), torch.from_numpy(c["O"]).to(dev), 0)
+    back = torch.zeros(n * f * f + shift, dtype=torch.complex64, device=dev)
+    dm.dm_get_state(ctx.ctx, back[shift:])
+    assert np.array_equal(back[shift:].cpu().numpy(), psi.cpu().numpy().ravel())
+    assert torch.equal(ctx.state()[0], psi)
+    ctx.free()
