@@ -962,8 +962,10 @@ dm_status launch_iteration(dm_ctx* c, bool psi_err) {
     DM_LAUNCHED(c, "k_probe_partial");
     DM_TRY(phase_end(c, mk));
     DM_TRY(phase_begin(c, DM_PHASE_PROBE_FINAL, &mk));
-    hipLaunchKernelGGL(dmk::k_probe_final, dim3(n_fblk(F), n), dim3(64 * (dmk::kFinalModes + 1)), 0,
-                       c->stream, c->scan_dev(), M, FF);
+    // waves for the modes there are: with always eight, three iterations of five scans of
+    // 3 modes x 128^2 took 4156 us instead of 4131
+    hipLaunchKernelGGL(dmk::k_probe_final, dim3(n_fblk(F), n),
+                       dim3(64 * (std::min(M, dmk::kFinalModes) + 1)), 0, c->stream, c->scan_dev(), M, FF);
     DM_LAUNCHED(c, "k_probe_final");
     return phase_end(c, mk);
   };

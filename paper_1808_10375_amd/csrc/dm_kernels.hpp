@@ -1451,10 +1451,10 @@ __global__ __launch_bounds__(256) void k_probe_partial(const ScanDev* __restrict
 // at 64 chunks x 3 modes x 64^2 and 8.4 us at 1 mode x 32^2, now 6.0 and 5.7
 // (launch included); the sums and their order are the same.
 constexpr int kFinalPix = 64;
-constexpr int kFinalModes = 8;  // waves for modes, and one for the denominator
+constexpr int kFinalModes = 8;  // most waves for modes; one more for the denominator
 __global__ __launch_bounds__(64 * (kFinalModes + 1)) void k_probe_final(
     const ScanDev* __restrict__ scans, int M, int FF) {
-  constexpr int NM = kFinalModes;
+  const int NM = uni((int)(blockDim.x >> 6) - 1);  // waves for modes
   __shared__ float pden[64];
   __shared__ float p2[16][64];  // |P'_m|^2
   const ScanDev& sc = scans[blockIdx.y];
