@@ -344,8 +344,15 @@ __device__ __forceinline__ void stage_padded_rows(float* bI, const float* Ij, in
   __syncthreads();
 }
 
+// Fused view update, one workgroup per view.  Below F = 128 a view's time is a
+// chain of latencies (two workgroups of 64^2 a compute unit, two waves a SIMD),
+// so whatever fits the 256 registers of that occupancy stays in them: the view,
+// the scale, and the probe and object values of the update, loaded before the
+// inverse transform.  With the scale through memory and the update's loads in
+// batches of four behind it, four iterations with checkpoint took 472 us at 407 x
+// 3 x 64^2 (now 445) and 2.88 ms at 3000 x 4 x 64^2 (now 2.35).
 template <int F, int V>
-__global__ __launch_bounds__(F * F / (16 * V)) void k_fourier_fused(
+__global__ __launch_bounds__(F * F / (16 * V), F < 128 ? 2 : 1) void k_fourier_fused(
     const ScanDev* __restrict__ scans, const int2* __restrict__ vmap, int total,
     const float2* __restrict__ tw, int M) {
   constexpr int B = F / 16;
@@ -395,8 +402,12 @@ __global__ __launch_bounds__(F * F / (16 * V)) void k_fourier_fused(
   // (F < 128 with one virtual thread, or F = 128 with two virtual threads per
   // 256-VGPR thread); otherwise it is read once more in the epilogue.
   constexpr bool kHold = (F < 128);
+  // the object values too cross the inverse transform; at F = 32 that would
+  // spill 21 of the 256 registers
+  constexpr bool kAheadO = kHold && F != 32;
   float2 a[V][16];
   float2 hold[kHold ? V : 1][kHold ? 16 : 1];
+  float g[kHold ? V : 1][kHold ? 16 : 1];
   {
     float S[V][16];
 #pragma unroll
@@ -416,7 +427,7 @@ __global__ __launch_bounds__(F * F / (16 * V)) void k_fourier_fused(
               cmul(bload2(rP, vF, sm + rowF(v, u1)), bload2(rO, vO, sO + rowO(v, u1)));
           a[v][u1] = make_float2(2.f * phi.x - ps.x, 2.f * phi.y - ps.y);
           if constexpr (kHold) hold[kHold ? v : 0][kHold ? u1 : 0] = ps;
-          if ((u1 & 7) == 7) __builtin_amdgcn_sched_barrier(0);
+          if (!kHold && (u1 & 7) == 7) __builtin_amdgcn_sched_barrier(0);
         }
       Frame2D<F, -1, V>::fwd(a, buf, twl, c, g0);
 #pragma unroll
@@ -431,13 +442,13 @@ __global__ __launch_bounds__(F * F / (16 * V)) void k_fourier_fused(
     const float inv_ff = 1.0f / (float)FF;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-      const int g = g0 + v * GS;
+      const int gr = g0 + v * GS;
 #pragma unroll
       for (int i = 0; i < 16 / B; ++i)
 #pragma unroll
         for (int l2 = 0; l2 < B; ++l2) {
           const int r = i * B + l2;
-          const int l = (g + B * i) + 16 * l2;
+          const int l = (gr + B * i) + 16 * l2;
           const float iv = fmaxf(bI[c * (F + 1) + l], 0.f);
           const float sv = S[v][r];
           S[v][r] = (sv > FLT_MIN) ? sqrtf(iv / sv) * inv_ff : 0.f;
@@ -446,9 +457,13 @@ __global__ __launch_bounds__(F * F / (16 * V)) void k_fourier_fused(
 #pragma unroll
     for (int v = 0; v < V; ++v)
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(S[v][r]), rg, vG,
-                                              (v * 16 + r) * NT * 4, 0);
+      for (int r = 0; r < 16; ++r) {
+        if constexpr (kHold)
+          g[kHold ? v : 0][kHold ? r : 0] = S[v][r];
+        else
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(S[v][r]), rg, vG,
+                                                (v * 16 + r) * NT * 4, 0);
+      }
   }
 
   // ---- pass 2: projected spectra back to views, modes in reverse order
@@ -471,7 +486,7 @@ __global__ __launch_bounds__(F * F / (16 * V)) void k_fourier_fused(
               cmul(bload2(rP, vF, sm + rowF(v, u1)), bload2(rO, vO, sO + rowO(v, u1)));
           a[v][u1] = make_float2(2.f * phi.x - ps.x, 2.f * phi.y - ps.y);
           if constexpr (kHold) hold[kHold ? v : 0][kHold ? u1 : 0] = ps;
-          if ((u1 & 7) == 7) __builtin_amdgcn_sched_barrier(0);
+          if (!kHold && (u1 & 7) == 7) __builtin_amdgcn_sched_barrier(0);
         }
       Frame2D<F, -1, V>::fwd(a, buf, twl, c, g0);
     }
@@ -479,7 +494,20 @@ __global__ __launch_bounds__(F * F / (16 * V)) void k_fourier_fused(
     for (int v = 0; v < V; ++v)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        a[v][r] = cscale(a[v][r], bload1(rg, vG, (v * 16 + r) * NT * 4));
+        a[v][r] = cscale(a[v][r], kHold ? g[kHold ? v : 0][kHold ? r : 0]
+                                        : bload1(rg, vG, (v * 16 + r) * NT * 4));
+    // the update's probe and object values cross the transform in registers
+    float2 prh[kHold ? V : 1][kHold ? 16 : 1], ovh[kHold ? V : 1][kHold ? 16 : 1];
+    if constexpr (kHold) {
+#pragma unroll
+      for (int v = 0; v < V; ++v)
+#pragma unroll
+        for (int u1 = 0; u1 < 16; ++u1) {
+          prh[kHold ? v : 0][kHold ? u1 : 0] = bload2(rP, vF, sm + rowF(v, u1));
+          if constexpr (kAheadO)
+            ovh[kHold ? v : 0][kHold ? u1 : 0] = bload2(rO, vO, sO + rowO(v, u1));
+        }
+    }
     Frame2D<F, 1, V>::inv(a, buf, twl, c, g0);
     // the psi' stores may alias later loads as far as the compiler knows:
     // each batch issues its loads before any of its stores
@@ -491,8 +519,10 @@ __global__ __launch_bounds__(F * F / (16 * V)) void k_fourier_fused(
         float2 pr[KB], ov[KB], pv[KB];
 #pragma unroll
         for (int k = 0; k < KB; ++k) {
-          pr[k] = bload2(rP, vF, sm + rowF(v, b + k));
-          ov[k] = bload2(rO, vO, sO + rowO(v, b + k));
+          pr[k] = kHold ? prh[kHold ? v : 0][kHold ? b + k : 0]
+                        : bload2(rP, vF, sm + rowF(v, b + k));
+          ov[k] = kAheadO ? ovh[kHold ? v : 0][kHold ? b + k : 0]
+                          : bload2(rO, vO, sO + rowO(v, b + k));
           pv[k] = kHold ? hold[kHold ? v : 0][kHold ? b + k : 0]
                         : bload2(rpsi, vF, sm + rowF(v, b + k));
         }

@@ -21,6 +21,16 @@ def test_probe_division_over_chunks_and_modes(seed, n, f, m):
     one_step_case(synth.random_case(seed, n, f, m, 2 * f + 7, 2 * f + 3, perturb=0.5))
 
 
+# the fused view kernel keeps a view's operands in registers below 128^2: one
+# mode (nothing transformed twice), two, three and 16 modes
+@pytest.mark.parametrize("seed,n,f,m", [(121, 9, 64, 1), (122, 33, 64, 2), (123, 17, 64, 3),
+                                        (124, 5, 64, 16), (125, 41, 32, 2), (126, 10, 32, 5),
+                                        (127, 11, 16, 3)])
+def test_fused_views_and_modes(seed, n, f, m):
+    say(f"case fused views seed={seed} N={n} F={f} M={m}")
+    one_step_case(synth.random_case(seed, n, f, m, 2 * f + 9, 2 * f + 4, perturb=0.5))
+
+
 # the column kernel of the BF16x3 form is compiled per mode count; the counts
 # the form's own tests leave out, with view counts that leave the persistent
 # blocks nothing (two views: fewer frames than blocks) or an uneven share
