@@ -137,9 +137,11 @@ int row_parts(int F) {
   return F / row_block(F);
 }
 
-// Whether a batch of frames of 188 or 200 pixels (views x modes) takes the
-// kernels of dm_mixed_few.hpp: start of the unrolled ones costs more than they
-// gain below these counts (two iterations with checkpoint, here against there:
+// Whether a scan with frames of 188 or 200 pixels (views x modes) takes the
+// kernels of dm_mixed_few.hpp.  The two sets round differently, so each scan of
+// a batch counts its own views: in a batch it runs what it runs alone.
+// The start of the unrolled kernels costs more than they gain below these
+// counts (two iterations with checkpoint, here against there:
 // 188^2 x 1 mode 145 / 194 us at 12 frames, 281 / 287 at 84, 405 / 406 at 150;
 // x 4 511 / 522 at 240; x 2 3113 / 2798 at 1600; 200^2 251 / 259 at 60 and 296 /
 // 282 at 90 frames).
@@ -396,6 +398,7 @@ struct dm_ctx {
   // was last set (dm_set_state): their error records are not valid
   int first_iter = 0;
   int total_views = 0, total_tiles = 0, total_chunks = 0;
+  int few_views = 0;  // leading entries of vmap: the views of the is_few scans
   int stream_slots = 0;
   dm_tuning tune{};
   // graph of one iteration
@@ -549,7 +552,7 @@ hipError_t set_mixed_lds(int M) {
   return e;
 }
 
-// eps_psi partials per view that the mixed-radix kernels of a batch write
+// eps_psi partials per view that the mixed-radix kernels of a scan write
 int mixed_parts(int F, int views, int M) {
   if (is_few(F, views, M)) return row_parts(F);
   return F == 188 ? dmk::Mix<188>::LB : dmk::Mix<200>::LB;
@@ -613,7 +616,7 @@ dm_status apply_tuning(dm_ctx* c, const dm_tuning& t) {
     v.C = S.C;
     v.chunk = S.chunk;
     v.n_psi_parts = is_bf16x3(S.d)  ? 2 * S.d.n_frames
-                    : is_mixed(c->F) ? S.d.n_frames * mixed_parts(c->F, c->total_views, c->M)
+                    : is_mixed(c->F) ? S.d.n_frames * mixed_parts(c->F, S.d.n_frames, c->M)
                     : t.view_path == DM_VIEWS_THREE_KERNEL ? L.n_psi_parts_multi
                                     : L.n_psi_parts_fused;
     v.beta = S.d.beta;
@@ -630,12 +633,13 @@ dm_status apply_tuning(dm_ctx* c, const dm_tuning& t) {
   DM_HIP(c, hipMemcpyAsync(c->cmap(), cmap.data(), cmap.size() * sizeof(int2),
                            hipMemcpyHostToDevice, c->stream));
   if (t.view_path == DM_VIEWS_THREE_KERNEL && is_mixed(c->F)) {
-    if (is_few(c->F, c->total_views, c->M)) {
+    if (c->few_views) {
       const int lds = (int)few_cols_lds_bytes(c->F, c->M, few_cols_per_block(c->F, c->M));
       const void* k = c->F == 188 ? reinterpret_cast<const void*>(dmk::k_few_cols<188>)
                                   : reinterpret_cast<const void*>(dmk::k_few_cols<200>);
       DM_HIP(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-    } else {
+    }
+    if (c->few_views < c->total_views) {
       DM_HIP(c, c->F == 188 ? set_mixed_lds<188>(c->M) : set_mixed_lds<200>(c->M));
     }
   } else if (t.view_path == DM_VIEWS_THREE_KERNEL) {
@@ -722,22 +726,23 @@ dm_status launch_views_multipass(dm_ctx* c, bool direct) {
 template <int F, bool ONE>
 dm_status launch_views_mixed_modes(dm_ctx* c, bool direct) {
   using C = dmk::Mix<F>;
-  const int M = c->M, blocks = c->total_views * C::LB;
+  const int M = c->M, blocks = (c->total_views - c->few_views) * C::LB;
+  const int2* const vmap = c->vmap() + c->few_views;
   hipLaunchKernelGGL(dmk::k_mix_rows_fwd<F>, dim3(blocks, M), dim3(64), 0, c->stream,
-                     c->scan_dev(), c->vmap(), c->tw(), M);
+                     c->scan_dev(), vmap, c->tw(), M);
   DM_LAUNCHED(c, "k_mix_rows_fwd");
   hipLaunchKernelGGL((dmk::k_mix_cols<F, ONE>), dim3(blocks),
                      dim3(64 * dmk::mix_cols_waves(M)), dmk::mix_cols_lds<F>(M), c->stream,
-                     c->scan_dev(), c->vmap(), c->tw(), M, direct ? 1 : 0);
+                     c->scan_dev(), vmap, c->tw(), M, direct ? 1 : 0);
   DM_LAUNCHED(c, "k_mix_cols");
   const dim3 bi(64 * std::min(M, dmk::kMixWaves));
   const size_t li = dmk::mix_inv_lds<F>(M);
   if (direct)
     hipLaunchKernelGGL((dmk::k_mix_rows_inv<F, true, ONE>), dim3(blocks), bi, li, c->stream,
-                       c->scan_dev(), c->vmap(), c->tw(), M);
+                       c->scan_dev(), vmap, c->tw(), M);
   else
     hipLaunchKernelGGL((dmk::k_mix_rows_inv<F, false, ONE>), dim3(blocks), bi, li, c->stream,
-                       c->scan_dev(), c->vmap(), c->tw(), M);
+                       c->scan_dev(), vmap, c->tw(), M);
   DM_LAUNCHED(c, "k_mix_rows_inv");
   return DM_OK;
 }
@@ -748,19 +753,19 @@ template <int F>
 dm_status launch_views_few(dm_ctx* c, bool direct) {
   using C = dmk::Few<F>;
   const int M = c->M;
-  hipLaunchKernelGGL(dmk::k_few_rows_fwd<F>, dim3(c->total_views, C::NBLK), dim3(C::NT), 0,
+  hipLaunchKernelGGL(dmk::k_few_rows_fwd<F>, dim3(c->few_views, C::NBLK), dim3(C::NT), 0,
                      c->stream, c->scan_dev(), c->vmap(), c->tw(), M);
   DM_LAUNCHED(c, "k_few_rows_fwd");
   const int cb = few_cols_per_block(F, M);
-  hipLaunchKernelGGL(dmk::k_few_cols<F>, dim3(c->total_views * ((F + cb - 1) / cb)),
+  hipLaunchKernelGGL(dmk::k_few_cols<F>, dim3(c->few_views * ((F + cb - 1) / cb)),
                      dim3(few_cols_threads(F, M, cb)), few_cols_lds_bytes(F, M, cb), c->stream,
                      c->scan_dev(), c->vmap(), c->tw(), M, cb, direct ? 1 : 0);
   DM_LAUNCHED(c, "k_few_cols");
   if (direct)
-    hipLaunchKernelGGL(dmk::k_few_rows_inv_direct<F>, dim3(c->total_views, C::NBLK),
+    hipLaunchKernelGGL(dmk::k_few_rows_inv_direct<F>, dim3(c->few_views, C::NBLK),
                        dim3(C::NT), 0, c->stream, c->scan_dev(), c->vmap(), c->tw(), M);
   else
-    hipLaunchKernelGGL(dmk::k_few_rows_inv<F>, dim3(c->total_views, C::NBLK), dim3(C::NT), 0,
+    hipLaunchKernelGGL(dmk::k_few_rows_inv<F>, dim3(c->few_views, C::NBLK), dim3(C::NT), 0,
                        c->stream, c->scan_dev(), c->vmap(), c->tw(), M);
   DM_LAUNCHED(c, "k_few_rows_inv");
   return DM_OK;
@@ -768,7 +773,8 @@ dm_status launch_views_few(dm_ctx* c, bool direct) {
 
 template <int F>
 dm_status launch_views_mixed(dm_ctx* c, bool direct) {
-  if (is_few(F, c->total_views, c->M)) return launch_views_few<F>(c, direct);
+  if (c->few_views) DM_TRY(launch_views_few<F>(c, direct));
+  if (c->few_views == c->total_views) return DM_OK;
   return c->M == 1 ? launch_views_mixed_modes<F, true>(c, direct)
                    : launch_views_mixed_modes<F, false>(c, direct);
 }
@@ -1112,7 +1118,7 @@ dm_status batch_init(dm_ctx** out, int n_scans, const dm_desc* descs, const floa
   c->flags = descs[0].flags;
   c->stream = reinterpret_cast<hipStream_t>(stream);
   c->ws = reinterpret_cast<char*>(ws);
-  std::vector<int2> vmap;
+  std::vector<int2> vmap, vmap_few;
   for (int s = 0; s < n_scans; ++s) {
     dm_ctx::Scan S;
     S.d = descs[s];
@@ -1123,9 +1129,12 @@ dm_status batch_init(dm_ctx** out, int n_scans, const dm_desc* descs, const floa
     S.O0 = O0s[s];
     S.pos.assign(poss[s], poss[s] + 2 * (size_t)S.d.n_frames);
     S.order = spatial_order(S.d, S.pos);
-    for (int j : S.order) vmap.push_back(make_int2(s, j));
+    const bool few = is_mixed(c->F) && is_few(c->F, S.d.n_frames, c->M);
+    for (int j : S.order) (few ? vmap_few : vmap).push_back(make_int2(s, j));
     c->scans.push_back(std::move(S));
   }
+  c->few_views = (int)vmap_few.size();
+  vmap.insert(vmap.begin(), vmap_few.begin(), vmap_few.end());
   c->total_views = (int)vmap.size();
   c->stream_slots = stream_slots(n_scans, descs);
   auto bail = [&](dm_status e) {
