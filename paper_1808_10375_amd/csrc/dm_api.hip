@@ -525,7 +525,17 @@ std::vector<int> spatial_order(const dm_desc& d, const std::vector<int>& pos) {
   return order;
 }
 
-hipError_t set_cols_lds(int F, int bytes) {
+// Dynamic LDS limits.  The limit belongs to the kernel, not to a context: it is
+// set to the most that any mode count takes, so that a context of fewer modes
+// leaves it as a live one of more modes needs it.
+template <class Bytes>
+hipError_t set_lds_limit(const void* kernel, int max_modes, Bytes&& bytes) {
+  size_t most = 0;
+  for (int m = 1; m <= max_modes; ++m) most = std::max(most, (size_t)bytes(m));
+  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+}
+
+hipError_t set_cols_lds(int F) {
   const void* k = nullptr;
   switch (F) {
     case 16: k = reinterpret_cast<const void*>(dmk::k_cols<16>); break;
@@ -534,22 +544,27 @@ hipError_t set_cols_lds(int F, int bytes) {
     case 128: k = reinterpret_cast<const void*>(dmk::k_cols<128>); break;
     case 256: k = reinterpret_cast<const void*>(dmk::k_cols<256>); break;
   }
-  return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  return set_lds_limit(k, DM_MAX_PAIRS,
+                       [=](int m) { return cols_lds_bytes(F, m, cols_per_block(F, m)); });
 }
 
-// dynamic LDS of the mixed-radix kernels (one mode needs no more than 64 KB)
+// (one mode takes kernels of its own, which need no more than 64 KB)
 template <int F>
-hipError_t set_mixed_lds(int M) {
-  if (M < 2) return hipSuccess;
+hipError_t set_mixed_lds() {
   const void* inv[2] = {reinterpret_cast<const void*>(dmk::k_mix_rows_inv<F, false, false>),
                         reinterpret_cast<const void*>(dmk::k_mix_rows_inv<F, true, false>)};
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(dmk::k_mix_cols<F, false>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)dmk::mix_cols_lds<F>(M));
+  hipError_t e = set_lds_limit(reinterpret_cast<const void*>(dmk::k_mix_cols<F, false>),
+                               DM_MAX_MODES, dmk::mix_cols_lds<F>);
   for (int k = 0; k < 2 && e == hipSuccess; ++k)
-    e = hipFuncSetAttribute(inv[k], hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)dmk::mix_inv_lds<F>(M));
+    e = set_lds_limit(inv[k], DM_MAX_MODES, dmk::mix_inv_lds<F>);
   return e;
+}
+
+hipError_t set_few_lds(int F) {
+  const void* k = F == 188 ? reinterpret_cast<const void*>(dmk::k_few_cols<188>)
+                           : reinterpret_cast<const void*>(dmk::k_few_cols<200>);
+  return set_lds_limit(k, DM_MAX_MODES,
+                       [=](int m) { return few_cols_lds_bytes(F, m, few_cols_per_block(F, m)); });
 }
 
 // eps_psi partials per view that the mixed-radix kernels of a scan write
@@ -633,19 +648,11 @@ dm_status apply_tuning(dm_ctx* c, const dm_tuning& t) {
   DM_HIP(c, hipMemcpyAsync(c->cmap(), cmap.data(), cmap.size() * sizeof(int2),
                            hipMemcpyHostToDevice, c->stream));
   if (t.view_path == DM_VIEWS_THREE_KERNEL && is_mixed(c->F)) {
-    if (c->few_views) {
-      const int lds = (int)few_cols_lds_bytes(c->F, c->M, few_cols_per_block(c->F, c->M));
-      const void* k = c->F == 188 ? reinterpret_cast<const void*>(dmk::k_few_cols<188>)
-                                  : reinterpret_cast<const void*>(dmk::k_few_cols<200>);
-      DM_HIP(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-    }
-    if (c->few_views < c->total_views) {
-      DM_HIP(c, c->F == 188 ? set_mixed_lds<188>(c->M) : set_mixed_lds<200>(c->M));
-    }
+    if (c->few_views) DM_HIP(c, set_few_lds(c->F));
+    if (c->few_views < c->total_views && c->M > 1)
+      DM_HIP(c, c->F == 188 ? set_mixed_lds<188>() : set_mixed_lds<200>());
   } else if (t.view_path == DM_VIEWS_THREE_KERNEL) {
-    const int MT = c->M * c->L;
-    const int lds = (int)cols_lds_bytes(c->F, MT, cols_per_block(c->F, MT));
-    DM_HIP(c, set_cols_lds(c->F, lds));
+    DM_HIP(c, set_cols_lds(c->F));
   }
   DM_HIP(c, hipStreamSynchronize(c->stream));
   return DM_OK;
