@@ -211,7 +211,7 @@ ScanLayout scan_layout(const dm_desc& d) {
   };
   L.psi = take(N * M * FF * c8);
   L.opart = take(N * NL * FF * c8);
-  L.gscr = d.frame <= 128 ? take(N * FF * 4) : 0;
+  L.gscr = d.frame == 128 ? take(N * FF * 4) : 0;
   L.tspec = has_spectrum_buffer(d) ? take(N * M * spectrum_frame(d.frame) * c8) : 0;
   L.P = take(M * FF * c8);
   L.O = take(NL * d.obj_h * d.obj_w * c8);
@@ -611,7 +611,7 @@ dm_status apply_tuning(dm_ctx* c, const dm_tuning& t) {
     v.pos = c->sat<int>(s, L.pos);
     v.order = c->sat<int>(s, L.order);
     v.opart = c->sat<float2>(s, L.opart);
-    v.gscr = S.d.frame <= 128 ? c->sat<float>(s, L.gscr) : nullptr;
+    v.gscr = S.d.frame == 128 ? c->sat<float>(s, L.gscr) : nullptr;
     v.tspec = L.tspec ? c->sat<float2>(s, L.tspec) : nullptr;
     v.D = c->sat<float>(s, L.D);
     v.num_part = c->sat<float2>(s, L.num_part);

@@ -33,7 +33,8 @@ struct ScanDev {
   const int* pos;         // [N][2]
   const int* order;       // [N] views in spatial order
   float2* opart;          // [N][L][F][F] per-view object numerators
-  float* gscr;            // [N][F][F] per-view modulus scale (fused path)
+  float* gscr;            // [N][F][F] per-view modulus scale (fused path at
+                          // F = 128; null below, where it stays in registers)
   float2* tspec;          // [N][L M][F][F] spectrum buffer (three-kernel path)
   float* D;               // [F][F] mode power
   float2* num_part;       // [Cmax][M][F][F]
@@ -376,18 +377,23 @@ __global__ __launch_bounds__(F * F / (16 * V), F < 128 ? 2 : 1) void k_fourier_f
   const float2* __restrict__ O = sc.O;
   const kidx_t pos = kidx(sc.pos);
   float2* __restrict__ opart = sc.opart;
-  float* __restrict__ gscr = sc.gscr;
   float* __restrict__ err_psi = sc.err_psi;
   const int H = uni(sc.H), W = uni(sc.W);
   const float beta = sc.beta;
   const int c = t % F;
   const int g0 = wave_uniform_div<F>(t);
   const int y0 = uni(pos[2 * j]), x0 = uni(pos[2 * j + 1]);
-  // buffers: this view's modes, the probe, the object, this view's scale
+  // The view is held in registers through both transforms when they fit
+  // (F < 128 with one virtual thread, or F = 128 with two virtual threads per
+  // 256-VGPR thread); otherwise it is read once more in the epilogue.
+  constexpr bool kHold = (F < 128);
+  // buffers: this view's modes, the probe, the object, and this view's scale
+  // where it passes through memory
   const rsrc_t rpsi = make_rsrc(psi + (size_t)j * M * FF, (uint32_t)(M * FF * 8));
   const rsrc_t rP = make_rsrc(P, (uint32_t)(M * FF * 8));
   const rsrc_t rO = make_rsrc(O, (uint32_t)((size_t)H * W * 8));
-  const rsrc_t rg = make_rsrc(gscr + (size_t)j * FF, (uint32_t)(FF * 4));
+  const rsrc_t rg = make_rsrc(kHold ? nullptr : sc.gscr + (size_t)j * FF,
+                              kHold ? 0u : (uint32_t)(FF * 4));
   // per-lane byte offsets of the first virtual thread (row g0, column c);
   // the other virtual threads and rows differ by wave-uniform offsets
   const int vF = (g0 * F + c) * 8;
@@ -398,10 +404,6 @@ __global__ __launch_bounds__(F * F / (16 * V), F < 128 ? 2 : 1) void k_fourier_f
   auto rowF = [&](int v, int u1) { return (B * u1 + v * GS) * F * 8; };
   auto rowO = [&](int v, int u1) { return (B * u1 + v * GS) * W * 8; };
 
-  // The view is held in registers through both transforms when they fit
-  // (F < 128 with one virtual thread, or F = 128 with two virtual threads per
-  // 256-VGPR thread); otherwise it is read once more in the epilogue.
-  constexpr bool kHold = (F < 128);
   // the object values too cross the inverse transform; at F = 32 that would
   // spill 21 of the 256 registers
   constexpr bool kAheadO = kHold && F != 32;
