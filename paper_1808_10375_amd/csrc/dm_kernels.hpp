@@ -41,7 +41,7 @@ struct ScanDev {
   float* den_part;        // [Cmax][F][F]
   float* err_psi;         // [n_psi_parts][2]
   float* err_obj;         // [ntiles_max][2]
-  float* err_probe;       // [n_pblk][M][2]
+  float* err_probe;       // [n_fblk][M][2]
   const int* tile_ptr;    // [ntiles + 1]
   const int* tile_views;  // [nnz]
   int* counter;           // iteration counter of this scan
@@ -863,9 +863,10 @@ __global__ __launch_bounds__(F * F / (16 * V)) void k_fourier_stream(
 // the probe sums read psi' through them, so that the probe, the object and
 // the intensities stay in the caches (at 10000 x 8 x 256^2 the view update
 // takes 62.3 ms with the hints and 65.4 ms without; the probe sums 6.05
-// against 6.78 ms).  The mixed-radix kernels read the buffer along columns,
-// where neighbouring lanes share cache lines that the hint would give up:
-// their view update took 52 ms with it, against 28 ms.
+// against 6.78 ms).  The mixed-radix kernels for few frames, whose buffer is
+// row-major, read it along columns, where neighbouring lanes share cache lines
+// that the hint would give up: they do without (a view update of 10000 x 4 x
+// 188^2 through them took 52 ms with it, against 28 ms).
 typedef float ntf2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float2 ntl2(const float2* p) {
   const ntf2 v = __builtin_nontemporal_load(reinterpret_cast<const ntf2*>(p));
@@ -1594,7 +1595,7 @@ __device__ __forceinline__ float rel_norm(double d, double n) {
 // now 17.0 and 6.1 us.
 constexpr int kErrThreads = 1024;
 __global__ __launch_bounds__(kErrThreads) void k_errors(const ScanDev* __restrict__ scans,
-                                                        int n_pblk, int M,
+                                                        int n_fblk, int M,
                                                         int* __restrict__ flags,
                                                         int psi_valid) {
   constexpr int NT = kErrThreads, NW = NT / 64;
@@ -1633,7 +1634,7 @@ __global__ __launch_bounds__(kErrThreads) void k_errors(const ScanDev* __restric
   }
   for (int m = w; m < M; m += NW) {
     double a = 0, b = 0;
-    sum2(err_probe + m, lane * M, 64 * M, (n_pblk - 1) * M + 1, a, b);
+    sum2(err_probe + m, lane * M, 64 * M, (n_fblk - 1) * M + 1, a, b);
     a = wave_sum_d(a);
     b = wave_sum_d(b);
     if (lane == 0) { pm[m][0] = a; pm[m][1] = b; }

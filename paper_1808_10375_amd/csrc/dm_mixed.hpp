@@ -344,11 +344,16 @@ __device__ __forceinline__ void mix_inv_out(const float2 (&a)[Mix<F>::Q], float2
   }
 }
 
-// byte offset that every buffer drops (and offsets within a frame of it)
+// Byte offset of a dropped access: past the end of every buffer that is stored
+// to, with any offset within a frame added.  Only an object of 1 GiB and more
+// is larger (up to 2 GiB): a load of it then returns some value of the object
+// instead of 0, which like the 0 goes no further than its tile cell.
 constexpr int kMixOob = 0x40000000;
 
-// Byte offset of X0 of pair i in a k-major frame; X1 is 2 Q lines further.  Rows
-// past the frame hold zeros in the padding.
+// Byte offset of X0 of pair i in a k-major frame; X1 is 2 Q lines further.  The
+// padding's rows past the frame hold nothing of use (transforms of the last
+// rows again, which the column kernel neither reads nor scales): what is formed
+// from them is neither stored nor summed.
 template <int F>
 struct MixSpec {
   int base, step;

@@ -24,9 +24,12 @@ struct Conv {
 
 // Whether the 3x3 convolutions run on activations kept in chunk layout
 // (dmnet_conv.hpp): every channel count but the input's is then a multiple of
-// 32.  Other widths keep the kernels that gather their operands: their sums
-// run channel by channel over the taps, an order that chunks cannot follow,
-// and another order flips bfloat16 roundings of later layers.
+// 32.  Networks of other widths keep channel-last copies and the kernels that
+// gather their operands.  Where a convolution's input channels are no multiple
+// of 32 those sum channel by channel over the taps, an order that chunks cannot
+// follow (another order flips bfloat16 roundings of later layers); the others
+// of such a network sum as the chunks do, but would need both layouts side by
+// side.
 bool chunked(const dmnet_desc& d) {
   return !(d.flags & DMNET_FLAG_FP32_WEIGHTS) && d.base_ch % 32 == 0;
 }
@@ -365,7 +368,7 @@ struct ConvTile {
                                      (int)conv3_lds(NW)));
     hipLaunchKernelGGL((dmn::k_conv3<OT, PT, WO, NW>), g, dim3(64 * NW), kWeights + grp * per,
                        net->stream, c.s0, c.s1, c.H, c.W, c.n, dps, dpw, grp, c.A, c.bias, c.y16,
-                       c.y32, c.yc, c.y_ns, c.relu ? 1 : 0);
+                       c.y32, c.y_ns, c.relu ? 1 : 0);
     NET_LAUNCHED(net, "k_conv3");
     return DM_OK;
   }

@@ -85,9 +85,10 @@ __host__ __device__ inline int conv_row_step(int TP, int W) {
   return W + 1 < TP + 2 ? W + 1 : TP + 2;
 }
 
-// q / d of 0 <= q < 2^31 by a multiplication: a block's set-up divides about
-// ten positions per thread, which with real divisions took longer than its
-// products
+// q / d of 0 <= q < 2^31 by a multiplication (Granlund and Montgomery, "Division
+// by invariant integers using multiplication", PLDI 1994): a block's set-up
+// divides about ten positions per thread, which with real divisions took
+// longer than its products
 struct FastDiv {
   uint32_t m, s, d;
   FastDiv() = default;
@@ -114,8 +115,7 @@ __global__ __launch_bounds__(64 * NW) void k_conv3(ConvSrc s0, ConvSrc s1, int H
                                                const uint16_t* __restrict__ A,
                                                const float* __restrict__ bias,
                                                uint16_t* __restrict__ y16,
-                                               float* __restrict__ y32, int yc, long y_ns,
-                                               int relu) {
+                                               float* __restrict__ y32, long y_ns, int relu) {
   using C = ConvCfg<OT, PT, WO, NW>;
   constexpr int TP = C::TP, WG = C::WG, NT = 64 * NW, NA = WG / NT, G = kConvG;
   extern __shared__ nb_u32x4 lds[];
