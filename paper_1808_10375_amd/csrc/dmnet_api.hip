@@ -325,8 +325,8 @@ dm_status refresh_packed(dmnet* net) {
   return DM_OK;
 }
 
-// LDS of a block: two weight groups and the staged run of as many chunks as
-// fit beside them, all of them where they do; half of a compute unit's for
+// LDS of a block: two weight groups and beside them the staged run of all
+// chunks, or (ROWS) a tap row of as many as fit; half of a compute unit's for
 // blocks of 4 waves, all of it for 8
 constexpr size_t conv3_lds(int nw) { return (size_t)nw * 20 * 1024; }
 
@@ -349,7 +349,7 @@ struct ConvCall {
   int chunks() const { return s0.nch + s1.nch; }
 };
 
-template <int OT, int PT, int WO, int NW>
+template <int OT, int PT, int WO, int NW, bool ROWS = false>
 struct ConvTile {
   using C = dmn::ConvCfg<OT, PT, WO, NW>;
   static constexpr size_t kWeights = (size_t)2 * 16 * C::WG;
@@ -359,14 +359,14 @@ struct ConvTile {
            c.chunks() * conv3_chunk_bytes<C>(c.W) + kWeights <= conv3_lds(NW);
   }
   static dm_status launch(dmnet* net, const ConvCall& c) {
-    const size_t per = conv3_chunk_bytes<C>(c.W);
+    const size_t per = ROWS ? (size_t)(C::TP + 2) * 64 : conv3_chunk_bytes<C>(c.W);
     const int grp = std::min(c.chunks(), (int)((conv3_lds(NW) - kWeights) / per));
     const dmn::FastDiv dps((uint32_t)((c.H + 1) * (c.W + 1))), dpw((uint32_t)(c.W + 1));
     const dim3 g((unsigned)((c.positions() + C::TP - 1) / C::TP), (unsigned)(c.yc / C::TO));
-    NET_HIP(net, hipFuncSetAttribute(reinterpret_cast<const void*>(dmn::k_conv3<OT, PT, WO, NW>),
+    NET_HIP(net, hipFuncSetAttribute(reinterpret_cast<const void*>(dmn::k_conv3<OT, PT, WO, NW, ROWS>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)conv3_lds(NW)));
-    hipLaunchKernelGGL((dmn::k_conv3<OT, PT, WO, NW>), g, dim3(64 * NW), kWeights + grp * per,
+    hipLaunchKernelGGL((dmn::k_conv3<OT, PT, WO, NW, ROWS>), g, dim3(64 * NW), kWeights + grp * per,
                        net->stream, c.s0, c.s1, c.H, c.W, c.n, dps, dpw, grp, c.A, c.bias, c.y16,
                        c.y32, c.y_ns, c.relu ? 1 : 0);
     NET_LAUNCHED(net, "k_conv3");
@@ -377,7 +377,8 @@ struct ConvTile {
 // The block tile of a 3x3 matrix-core convolution (output channels x
 // positions): the largest that holds all input channels in LDS and still
 // gives the 256 compute units two blocks of 4 waves or one of 8; else the
-// smallest, whose blocks stage the channels in groups for every tap.
+// smallest that holds them; and where none does, blocks of 8 waves that stage
+// one tap row at a time.
 dm_status conv3(dmnet* net, const ConvCall& c) {
   if (c.yc % 64 == 0) {
     if (ConvTile<4, 4, 1, 4>::fits(c, 512)) return ConvTile<4, 4, 1, 4>::launch(net, c);
@@ -386,12 +387,14 @@ dm_status conv3(dmnet* net, const ConvCall& c) {
     if (ConvTile<2, 2, 2, 4>::fits(c, 512)) return ConvTile<2, 2, 2, 4>::launch(net, c);
     if (ConvTile<2, 2, 2, 8>::fits(c, 256)) return ConvTile<2, 2, 2, 8>::launch(net, c);
     if (ConvTile<2, 2, 2, 4>::fits(c, 1)) return ConvTile<2, 2, 2, 4>::launch(net, c);
-    return ConvTile<2, 2, 2, 8>::launch(net, c);
+    if (ConvTile<2, 2, 2, 8>::fits(c, 1)) return ConvTile<2, 2, 2, 8>::launch(net, c);
+    return ConvTile<2, 2, 2, 8, true>::launch(net, c);
   }
   if (ConvTile<2, 4, 1, 4>::fits(c, 512)) return ConvTile<2, 4, 1, 4>::launch(net, c);
   if (ConvTile<2, 4, 1, 8>::fits(c, 256)) return ConvTile<2, 4, 1, 8>::launch(net, c);
   if (ConvTile<1, 4, 2, 4>::fits(c, 1)) return ConvTile<1, 4, 2, 4>::launch(net, c);
-  return ConvTile<1, 4, 2, 8>::launch(net, c);
+  if (ConvTile<1, 4, 2, 8>::fits(c, 1)) return ConvTile<1, 4, 2, 8>::launch(net, c);
+  return ConvTile<1, 4, 2, 8, true>::launch(net, c);
 }
 
 // y = conv(x) (+ ReLU); x, y are per-sample-strided tensors

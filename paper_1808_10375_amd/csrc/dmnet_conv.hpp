@@ -54,9 +54,11 @@ __global__ void k_pack3(const uint16_t* __restrict__ w, int co, int ci,
 // constant offset of q and a run of TP consecutive q needs one run of
 // TP + 2 PW + 2 inputs (PW = W + 1) -- or, when the rows are longer than the
 // tile, three runs of TP + 2.  A block stages that run once for all channels
-// (a group of `grp` chunks at a time where LDS does not hold them all) and
-// reads every tap's operand there: 16 lanes x 4 parts of 16 bytes are 1 KB of
-// consecutive LDS, free of bank conflicts.  The weights pass through LDS too,
+// and reads every tap's operand there: 16 lanes x 4 parts of 16 bytes are 1 KB of
+// consecutive LDS, free of bank conflicts.  Where LDS does not hold all channels
+// (ROWS), it takes one tap row after another, TP + 2 inputs of all channels, or
+// of `grp` chunks at a time, which come again for each tap of the row (the
+// products run tap by tap).  The weights pass through LDS too,
 // kConvG steps (tap, chunk) at a time in two buffers, the group after next on
 // its way to registers.  Outputs at padding positions are dropped (3% of the
 // work at W = 64, 27% at W = 8).
@@ -65,11 +67,13 @@ __global__ void k_pack3(const uint16_t* __restrict__ w, int co, int ci,
 // step of 16 products (256 cycles of a SIMD) reads 8 KB of LDS per wave, which
 // is the LDS rate; what bounds a block is the chain stage, products, store,
 // hidden by the other blocks of its compute unit.  64 samples of the 4-level
-// 32-channel network at 64 x 64: 26 us for 32 -> 32 channels at 64^2, 45 us
-// for 96 -> 32, 47 us for 192 -> 64 at 32^2.  With every wave reading its
+// 32-channel network at 64 x 64: 22-27 us for 32 -> 32 channels at 64^2, 42 us
+// for 96 -> 32, 42 us for 192 -> 64 at 32^2.  With every wave reading its
 // operands of every tap from the caches (k_conv3_mfma_cl), and a pass that
 // converts and transposes each input, the forward pass over 300 frames took
-// 4.4 ms against 2.1.
+// 4.4 ms against 2.0.  16 samples of 64 x 64 with 128, 256 and 512 channels take
+// 1.04 ms with ROWS; 1.52 ms with that kernel, and 1.68 ms when the groups were
+// staged with all three tap rows for every tap.
 // ---------------------------------------------------------------------------
 constexpr int kConvG = 4;  // steps per weight group
 
@@ -109,7 +113,7 @@ struct ConvSrc {
 
 typedef unsigned int nb_u32x4 __attribute__((ext_vector_type(4)));
 
-template <int OT, int PT, int WO, int NW>
+template <int OT, int PT, int WO, int NW, bool ROWS>
 __global__ __launch_bounds__(64 * NW) void k_conv3(ConvSrc s0, ConvSrc s1, int H, int W, int n,
                                                FastDiv dps, FastDiv dpw, int grp,
                                                const uint16_t* __restrict__ A,
@@ -126,7 +130,7 @@ __global__ __launch_bounds__(64 * NW) void k_conv3(ConvSrc s0, ConvSrc s1, int H
   const int wo = wave % WO, wp = wave / WO;
   const int PW = W + 1, PS = (H + 1) * PW, HW = H * W;
   const int RS = conv_row_step(TP, W);
-  const int nx = (TP + 2 + 2 * RS) * 4;  // 16-byte parts of inputs per chunk
+  const int nx = (TP + 2 + (ROWS ? 0 : 2 * RS)) * 4;  // 16-byte parts of inputs per chunk
   const int q0 = blockIdx.x * TP, o0 = blockIdx.y * C::TO;
   const int n0 = s0.nch, up = s0.up, nch = n0 + s1.nch;
   const int H0 = H >> up, W0 = W >> up;
@@ -134,8 +138,9 @@ __global__ __launch_bounds__(64 * NW) void k_conv3(ConvSrc s0, ConvSrc s1, int H
   const nb_u32x4* __restrict__ b1 = reinterpret_cast<const nb_u32x4*>(s1.p);
   const size_t st0 = (size_t)n * H0 * W0 * 4, st1 = (size_t)n * HW * 4;
   const nb_u32x4 zero = {0u, 0u, 0u, 0u};
-  // chunks c0 .. c1 - 1 of the run to LDS, seven parts a thread in flight
-  auto stage = [&](int c0, int c1) {
+  // chunks c0 .. c1 - 1 of the run (of its tap row dy) to LDS, seven parts a
+  // thread in flight
+  auto stage = [&](int c0, int c1, int dy) {
     constexpr int U = 7;
     for (int i0 = t; i0 < nx; i0 += NT * U) {
       size_t p0[U], p1[U];
@@ -144,7 +149,9 @@ __global__ __launch_bounds__(64 * NW) void k_conv3(ConvSrc s0, ConvSrc s1, int H
       for (int k = 0; k < U; ++k) {
         const int id = i0 + NT * k, u = id >> 2;
         int q;
-        if (RS == PW) {
+        if (ROWS) {
+          q = q0 + (dy - 1) * PW - 1 + u;
+        } else if (RS == PW) {
           q = q0 - PW - 1 + u;
         } else {
           const int seg = u / (TP + 2);
@@ -196,13 +203,12 @@ __global__ __launch_bounds__(64 * NW) void k_conv3(ConvSrc s0, ConvSrc s1, int H
     for (int p = 0; p < PT; ++p) acc[o][p] = nb_f32x4{0.f, 0.f, 0.f, 0.f};
   const int xb = (wp * PT * 16 + (lane & 15)) * 4 + (lane >> 4);
   const int ab = wo * OT * 64 + lane;
-  const bool once = grp >= nch;
   load_w(0);
-  stage(0, once ? nch : grp);
+  stage(0, ROWS ? grp : nch, 0);
   store_w(0);
   if (groups > 1) load_w(1);
   __syncthreads();
-  int tap = 0, ch = 0;
+  int tap = 0, ch = 0, cg = 0;  // tap, chunk and (ROWS) chunk within its group
   for (int g = 0; g < groups; ++g) {
     // the other weight buffer's readers passed the barrier that ended group g - 1
     if (g + 1 < groups) store_w(g + 1);
@@ -211,13 +217,13 @@ __global__ __launch_bounds__(64 * NW) void k_conv3(ConvSrc s0, ConvSrc s1, int H
     for (int d = 0; d < G; ++d) {
       const int s = g * G + d;
       if (s < steps) {
-        if (!once && s > 0 && ch % grp == 0) {
+        const int dy = tap / 3, dx = tap - 3 * dy;
+        if (ROWS && s > 0 && cg == 0 && (grp < nch || dx == 0)) {
           __syncthreads();
-          stage(ch, ch + grp < nch ? ch + grp : nch);
+          stage(ch, ch + grp < nch ? ch + grp : nch, dy);
           __syncthreads();
         }
-        const int dy = tap / 3, dx = tap - 3 * dy;
-        const int xo = xb + (once ? ch : ch % grp) * nx + (dy * RS + dx) * 4;
+        const int xo = xb + (ROWS ? cg : ch) * nx + ((ROWS ? 0 : dy * RS) + dx) * 4;
         nb_s16x8 a[OT], b[PT];
 #pragma unroll
         for (int o = 0; o < OT; ++o)
@@ -229,7 +235,8 @@ __global__ __launch_bounds__(64 * NW) void k_conv3(ConvSrc s0, ConvSrc s1, int H
         for (int o = 0; o < OT; ++o)
 #pragma unroll
           for (int p = 0; p < PT; ++p) acc[o][p] = nb_mma(a[o], b[p], acc[o][p]);
-        if (++ch == nch) { ch = 0; ++tap; }
+        if (ROWS && ++cg == grp) cg = 0;
+        if (++ch == nch) { ch = cg = 0; ++tap; }
       }
     }
     __syncthreads();
