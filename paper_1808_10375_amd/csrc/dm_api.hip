@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <mutex>
 #include <new>
 #include <string>
@@ -137,16 +138,47 @@ int row_parts(int F) {
   return F / row_block(F);
 }
 
-// Whether a scan with frames of 188 or 200 pixels (views x modes) takes the
-// kernels of dm_mixed_few.hpp.  The two sets round differently, so each scan of
-// a batch counts its own views: in a batch it runs what it runs alone.
-// The start of the unrolled kernels costs more than they gain below these
-// counts (two iterations with checkpoint, here against there:
-// 188^2 x 1 mode 145 / 194 us at 12 frames, 281 / 287 at 84, 405 / 406 at 150;
-// x 4 511 / 522 at 240; x 2 3113 / 2798 at 1600; 200^2 251 / 259 at 60 and 296 /
-// 282 at 90 frames).
+// Frames (views x modes) of a scan from which the unrolled kernels of
+// dm_mixed.hpp are the faster ones.  Against them stand their cold start (each
+// compute unit fetches thousands of instructions) and wave slots that stay
+// empty: the column kernel's blocks have a wave per mode, and a compute unit
+// has room for 8 waves at 188^2 and 12 at 200^2, so that 5 modes leave 3 of 8
+// empty, 3 and 6 modes 2, and above 8 modes six waves take the modes in rounds,
+// of which 9 and 10 modes fill the last one badly.  An iteration, here against
+// there, in us:
+//   188^2  1 mode 286 / 290 at 280 frames, 535 / 455 at 512; 2 modes 351 / 355 at
+//   400, 447 / 437 at 512; 3 modes 329 / 357 at 399, 523 / 497 at 639; 4 modes 234 /
+//   241 at 280, 409 / 357 at 512; 5 modes 978 / 1061 at 1300, ratio 0.99 at 4000; 6
+//   modes 321 / 355 at 402, 526 / 516 at 642; 8 modes 187 / 208 at 200, 414 / 353 at
+//   512; 9 modes 1020 / 1063 at 1296, ratio 1.02 at 3996; 12 modes 458 / 499 at 516,
+//   572 / 539 at 636
+//   200^2  1 mode 225 / 229 at 200, 330 / 292 at 280; 2 modes 258 / 264 at 280, 395 / 358
+//   at 400; 3 modes 239 / 253 at 279, 365 / 336 at 399; 4 modes 193 / 196 at 200, 251 / 238
+//   at 280; 5 modes 359 / 372 at 400, 495 / 474 at 560; 6 modes 191 / 198 at 198, 365 / 350
+//   at 402; 7 modes 257 / 266 at 280, 357 / 316 at 399; 8 modes 144 / 112 at 80; 9 modes 378 /
+//   403 at 396, ratio 1.06 at 504; 12 modes 235 / 163 at 84
+long unrolled_from(int F, int M) {
+  constexpr long kNever = std::numeric_limits<long>::max();
+  if (F == 188) {
+    if (M == 5) return kNever;
+    if (M == 9 || M == 10) return 2000;
+    return M == 3 || M == 6 || M > 10 ? 640 : 512;
+  }
+  if (M == 8 || M > 9) return 80;
+  if (M == 5 || M == 9) return 500;
+  return M == 1 || M == 4 ? 220 : 330;
+}
+
+// Whether a scan with frames of 188 or 200 pixels takes the kernels of
+// dm_mixed_few.hpp.  The two sets round differently, so each scan of a batch
+// counts its own views: in a batch it runs what it runs alone.
 bool is_few(int F, int views, int M) {
-  return (long)views * M < (F == 188 ? 512 : 80);
+  const long frames = (long)views * M;
+  // 200^2 with five modes and more: while the blocks fit one round of one block
+  // a compute unit, none waits (118 / 104 us at 16 views x 5 modes, 132 / 156 at
+  // 20; 135 / 106 at 13 x 6, 160 / 173 at 23; 158 / 120 at 14 x 7, 166 / 183 at 20)
+  if (F == 200 && M >= 5 && frames >= 80 && views * dmk::Mix<200>::LB <= 256) return false;
+  return frames < unrolled_from(F, M);
 }
 
 // threads per line of the few-frame mixed-radix transforms (Q + 1)

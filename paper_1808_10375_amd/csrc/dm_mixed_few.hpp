@@ -3,9 +3,9 @@
 // has few frames: the same three kernels with the lines in LDS.  Their loops
 // are a few hundred instructions; the unrolled transforms of dm_mixed.hpp are
 // thousands, each fetched once from memory by every compute unit, which a
-// scan of a few frames waits for (12 x 1 x 188^2: 137 us for two iterations with
-// their checkpoint here, 195 us there; from about 500 frames at 188^2 and 80 at
-// 200^2 on the others are faster).  The spectrum buffer is row-major here.
+// scan of a few frames waits for (12 x 1 x 188^2: 130 us for two iterations with
+// their checkpoint here, 197 us there), and some mode counts leave a part of the
+// others' wave slots empty.  The spectrum buffer is row-major here.
 //
 // One length-F line is transformed with one level of the Cooley-Tukey split
 // n = Q n1 + n2, k = k1 + R k2:

@@ -47,9 +47,9 @@ def state(ctx):
 
 
 # kernels whose blocks take over 64 KB at the first mode count: the unrolled
-# column and inverse row kernels of 188^2 and 200^2 (views x modes of at least
-# 512 and 80), the column kernel of the power-of-two frames (16 modes of 16^2)
-@pytest.mark.parametrize("f,many,few", [(200, (10, 8), (40, 2)), (188, (32, 16), (256, 2)),
+# column and inverse row kernels of 188^2 and 200^2 (both contexts with frames
+# enough to take them), the column kernel of the power-of-two frames (16 modes of 16^2)
+@pytest.mark.parametrize("f,many,few", [(200, (10, 8), (165, 2)), (188, (40, 16), (256, 2)),
                                         (16, (9, 16), (9, 1))])
 def test_older_context_of_more_modes_still_runs(f, many, few):
     _torch()

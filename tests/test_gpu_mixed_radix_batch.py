@@ -13,12 +13,13 @@ def same(a, b):
     return a == b or (np.isnan(a) and np.isnan(b))
 
 
-# (frame, modes, frames of the scans): the unrolled kernels start at 512 frames
-# (views x modes) at 188^2 and at 80 at 200^2.  Scans below that count which
-# together reach it; both kinds in one batch, the larger scan first; scans
-# above it only, with and without whole groups of eight views.
-@pytest.mark.parametrize("f,m,sizes", [(200, 1, (30, 41, 9)), (188, 2, (130, 128)),
-                                       (200, 1, (83, 20, 96, 7)), (200, 3, (27, 40)),
+# (frame, modes, views of the scans): the unrolled kernels start at 512 frames
+# (views x modes) at 188^2 x 2 modes, at 220 at 200^2 x 1, at 330 at 200^2 x 3, at 500
+# or with 9 to 19 views at 200^2 x 9.  Scans below that count which together reach
+# it; both kinds in one batch, the larger scan first; scans above it only, with
+# and without whole groups of eight views.
+@pytest.mark.parametrize("f,m,sizes", [(200, 1, (100, 90, 41)), (188, 2, (130, 128)),
+                                       (200, 1, (225, 20, 230, 7)), (200, 3, (112, 115)),
                                        (200, 9, (11, 9))])
 @pytest.mark.parametrize("last", [False, True])
 def test_mixed_radix_batch_equals_each_scan_alone(f, m, sizes, last):
