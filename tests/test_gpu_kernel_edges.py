@@ -41,10 +41,10 @@ def test_bf16x3_mode_counts(seed, n, m):
     bf16x3.compare(synth.random_case(seed, n, 128, m, 190, 200, perturb=0.3))
 
 
-# the mixed-radix frames from the frame counts on where the unrolled kernels
-# run (512 at 188^2, 80 at 200^2; the last two just below): modes shared out
-# over the waves of a block (up to 8 one each; above, the column kernel takes
-# six waves, the inverse row kernel eight, with the last round part empty), the
+# the mixed-radix frames on both kernel sets (513 x 1 and 256 x 2 frames of 188^2
+# and 13 x 7 and 8 x 13 of 200^2 run the unrolled kernels): modes shared out over
+# the waves of a block (up to 8 one each; above, the column kernel takes six
+# waves, the inverse row kernel eight, with the last round part empty), the
 # single-mode forms, and view counts with whole groups of eight views per XCD
 # map and a remainder
 @pytest.mark.parametrize("seed,n,f,m", [(101, 513, 188, 1), (102, 80, 200, 1), (103, 256, 188, 2),
@@ -55,9 +55,9 @@ def test_mixed_radix_modes_and_views(seed, n, f, m):
     one_step_case(synth.random_case(seed, n, f, m, f + 60, f + 55, perturb=0.5))
 
 
-# a checkpoint's views go in and out bit for bit: just below and above the size
-# from which a kernel streams them (64 MB; blocks of 4096 words of 16 bytes, the
-# last one partial), and from and to addresses 8 bytes off a 16-byte boundary
+# a checkpoint's views go in and out bit for bit: below and above the size from
+# which a kernel streams them (64 MB; blocks of 1024 words of 16 bytes, the last
+# one partial), and from and to addresses 8 bytes off a 16-byte boundary
 @pytest.mark.parametrize("n,f,shift", [(63, 256, 0), (129, 256, 0), (238, 188, 0), (130, 256, 1)])
 def test_checkpoint_views_round_trip(n, f, shift):
     import torch

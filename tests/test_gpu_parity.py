@@ -322,7 +322,7 @@ def test_mode_power_matches_the_probe_and_the_oracle(seed, n, f, m, h, w):
 
 MIXED = [
     # (seed, N, F, M, H, W, perturb): the paper's frame edges 188 = 4 x 47 and
-    # 200 = 8 x 25.  Column blocks of the column kernel (at most 512 threads,
+    # 200 = 8 x 25, in scans of few frames.  Column blocks of their column kernel (at most 512 threads,
     # M (Q + 1) threads per column): F = 188 with one mode takes 8 columns, the
     # last block partial (188 = 23 x 8 + 4); 4 modes at 188 and 8 modes at 200
     # take 2 columns, 3 modes at 200 take 4, and 16 modes one column.  Row
